@@ -40,10 +40,6 @@ PEAK_TFLOPS = {"f64": 78.6, "f32": 157.3, "bf16": 2500.0}
 MEASURED_TRAFFIC = {
     ("al32", "mixed"): {
         "stencil": (490.1e6, 226.5e6),
-        "nl_scatter": (455.9e6, 226.5e6),
-        # the filter steps' two-piece integrals (24 of the 25 applications) plus
-        # the reduction of their partials
-        "nl_gather": (286.3e6 + 37.8e6, 32.5e6 + 0.4e6),
     },
 }
 

@@ -210,17 +210,10 @@ dk_status dk_create(dk_ctx** out, int nx, int ny, int nz, double lx, double ly, 
 
 static void free_tables(dk_ctx* c) {
   hipFree(c->chi64); c->chi64 = nullptr;
-  hipFree(c->chi32); c->chi32 = nullptr;
-  hipFree(c->chi_pieces); c->chi_pieces = nullptr;
-  c->chi_pieces_bytes = 0;
   c->dchi64 = nullptr;  // part of the chi64 allocation
   hipFree(c->gamma_dev); c->gamma_dev = nullptr;
   hipFree(c->atom_dev); c->atom_dev = nullptr;
-  hipFree(c->mask_t); c->mask_t = nullptr;
-  hipFree(c->klist); c->klist = nullptr;
-  hipFree(c->kcount); c->kcount = nullptr;
-  free_gather_chunks(c);
-  c->n_groups = 0;
+  free_sweep_tables(c);
   c->n_proj = 0;
   c->model_channels = 0;
 }
@@ -305,35 +298,18 @@ dk_status dk_set_projectors(dk_ctx* c, int n_proj, int n_atoms, const int64_t* o
     c->gamma_h.push_back(gamma[p]);
     c->atom_h.push_back(atom[p]);
   }
-  // block masks
-  const long gblocks = (ng + 63) / 64;
-  const int ptiles = (n_proj + 63) / 64;
-  std::vector<uint8_t> mt((size_t)ptiles * gblocks, 0);
-  for (int p = 0; p < n_proj; ++p)
-    for (long x = 0; x < ng; ++x)
-      if (dense[(size_t)p * ng + x] != 0.0) {
-        mt[(size_t)(p / 64) * gblocks + x / 64] = 1;
-      }
-  c->mask_t_stride = gblocks;
-  std::vector<float> dense32(dense.begin(), dense.end());
   // chi and its three finite-difference gradients are one N_grid x 4 n_proj
   // table, so the force contractions read the block once
   DK_HIP(c, hipMalloc(&c->chi64, 4 * dense.size() * sizeof(double)));
   c->dchi64 = c->chi64 + dense.size();
-  if (c->precision == DK_PREC_MIXED) DK_HIP(c, hipMalloc(&c->chi32, dense.size() * sizeof(float)));
   DK_HIP(c, hipMalloc(&c->gamma_dev, n_proj * sizeof(double)));
   DK_HIP(c, hipMalloc(&c->atom_dev, n_proj * sizeof(int)));
-  DK_HIP(c, hipMalloc(&c->mask_t, mt.size()));
   DK_HIP(c, hipMemcpy(c->chi64, dense.data(), dense.size() * sizeof(double), hipMemcpyHostToDevice));
-  if (c->chi32) DK_HIP(c, hipMemcpy(c->chi32, dense32.data(), dense32.size() * sizeof(float), hipMemcpyHostToDevice));
   DK_HIP(c, hipMemcpy(c->gamma_dev, c->gamma_h.data(), n_proj * sizeof(double), hipMemcpyHostToDevice));
   DK_HIP(c, hipMemcpy(c->atom_dev, c->atom_h.data(), n_proj * sizeof(int), hipMemcpyHostToDevice));
-  DK_HIP(c, hipMemcpy(c->mask_t, mt.data(), mt.size(), hipMemcpyHostToDevice));
   c->n_proj = n_proj;
   DK_HIP(c, fd_gradient_tables(c));
-  DK_HIP(c, projector_group_lists(c));
-  DK_HIP(c, build_gather_chunks(c));
-  DK_HIP(c, build_table_pieces(c));
+  DK_HIP(c, build_sweep_tables(c));
   return finish(c, "dk_set_projectors");
 }
 
@@ -368,18 +344,14 @@ dk_status dk_set_projector_model(dk_ctx* c, int n_atoms, const double* pos, int 
     c->atom_h.clear();
     return DK_OK;
   }
-  const long gblocks = (ng + 63) / 64;
-  const int ptiles = (n_proj + 63) / 64;
   const size_t table = (size_t)ng * n_proj;
   // keep the tables of the previous call when the sizes match (an ionic step)
-  if (n_proj != c->n_proj || !c->chi64 || (c->precision == DK_PREC_MIXED) != (c->chi32 != nullptr)) {
+  if (n_proj != c->n_proj || !c->chi64) {
     free_tables(c);
     DK_HIP(c, hipMalloc(&c->chi64, 4 * table * sizeof(double)));
     c->dchi64 = c->chi64 + table;
-    if (c->precision == DK_PREC_MIXED) DK_HIP(c, hipMalloc(&c->chi32, table * sizeof(float)));
     DK_HIP(c, hipMalloc(&c->gamma_dev, n_proj * sizeof(double)));
     DK_HIP(c, hipMalloc(&c->atom_dev, n_proj * sizeof(int)));
-    DK_HIP(c, hipMalloc(&c->mask_t, (size_t)ptiles * gblocks));
   }
   const size_t aux = 3 * (size_t)n_atoms + n_proj;
   if (aux > c->proj_aux_len) {
@@ -404,7 +376,6 @@ dk_status dk_set_projector_model(dk_ctx* c, int n_atoms, const double* pos, int 
         c->gamma_h.push_back(gamma[k]);
         c->atom_h.push_back(a);
       }
-  c->mask_t_stride = gblocks;
   double* pos_dev = c->proj_aux;
   double* norms_dev = c->proj_aux + 3 * (size_t)n_atoms;
   DK_HIP(c, hipMemcpyAsync(pos_dev, pos, 3 * (size_t)n_atoms * sizeof(double), hipMemcpyHostToDevice, c->stream));
@@ -413,9 +384,7 @@ dk_status dk_set_projector_model(dk_ctx* c, int n_atoms, const double* pos, int 
   DK_HIP(c, build_projector_tables(c, pos_dev, n_atoms, n_channels, l, rc, cutoff_rel, norms_dev));
   c->n_proj = n_proj;
   DK_HIP(c, fd_gradient_tables(c));
-  DK_HIP(c, projector_group_lists(c));
-  DK_HIP(c, build_gather_chunks(c));
-  DK_HIP(c, build_table_pieces(c));
+  DK_HIP(c, build_sweep_tables(c));
   std::vector<double> nrm(n_proj);
   DK_HIP(c, hipMemcpyAsync(nrm.data(), norms_dev, n_proj * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   dk_status s = finish(c, "dk_set_projector_model");

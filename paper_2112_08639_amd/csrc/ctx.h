@@ -25,42 +25,35 @@ struct dk_ctx {
   // projectors: dense column-major N_grid x n_proj tables (ld = ngrid)
   int n_proj = 0, n_atoms = 0;
   double* chi64 = nullptr;
-  float* chi32 = nullptr;
-  // mixed path, dense integrals over more than 64 projectors: the three bf16
-  // pieces of the table (split_planes layout, k = grid point), built with it
-  void* chi_pieces = nullptr;
-  size_t chi_pieces_bytes = 0;
   double* dchi64 = nullptr;  // grad_h chi along x, y, z: 3 tables following chi64 in one allocation
-  float* dchi32 = nullptr;
   double* gamma_dev = nullptr;
   int* atom_dev = nullptr;
   std::vector<double> gamma_h;
   std::vector<int> atom_h;
   double nl_bound = 0.0;  // sum over gamma_p > 0 of gamma_p h^3 |chi_p|^2
-  // block mask of the tables: mask_t[pt*mask_t_stride + gb] for 64-projector
-  // tiles x 64-point grid blocks
-  uint8_t* mask_t = nullptr;
-  long mask_t_stride = 0;
-  // per 64-point grid block, the 4-projector groups with a nonzero table entry
-  // there: klist[gb * n_groups + i] for i < kcount[gb], increasing
+  // compact tables of the nonlocal term (sweep.hip).  Per 64-point grid block, the
+  // 4-projector groups with a nonzero table entry there: klist[gb * n_groups + i] for
+  // i < kcount[gb], increasing; geoff their running count; the scatter (mixed) and
+  // integral operands, one entry per (block, live group); growrec the live slots of
+  // every (run, block)
   int* klist = nullptr;
   int* kcount = nullptr;
+  int* geoff = nullptr;
   int n_groups = 0;
-  // projector integrals over compact supports (gather.hip): chunks of
-  // consecutive 64-point blocks {first block, blocks, union offset, union
-  // length}, per (chunk, block) row the union slot -> table entry map and the
-  // live 16-row blocks, the occurrences of every group among the unions, and
-  // the compact (pre-split) table entries
+  long g_entries = 0;   // (block, live group) pairs
+  long g_capacity = 0;  // entries the tables have room for
+  void* gtab = nullptr;
+  float* stab = nullptr;
+  void* growrec = nullptr;
+  // beyond max_slots groups: chunks of consecutive blocks {first block, blocks, union
+  // offset, union length}, the row of each one's first block, and the occurrences of
+  // every group among the unions
   int n_gchunks = 0;
-  long g_rows = 0;     // sum of the union lengths
-  long g_entries = 0;  // (block, live group) pairs
-  void* gchunk = nullptr;
+  long g_rows = 0;  // sum of the union lengths
+  int* gchunk = nullptr;
   int* gqoff = nullptr;
-  int* gamap = nullptr;
-  unsigned* gbmask = nullptr;
   int* gocc_off = nullptr;
   int* gocc = nullptr;
-  void* gtab = nullptr;
   // device-built tables (dk_set_projector_model): atom positions (3 n_atoms)
   // followed by the projector norms |chi_p|^2 (n_proj)
   double* proj_aux = nullptr;
@@ -181,8 +174,9 @@ size_t stress_ws_bytes(const dk_ctx* c, int n_s);
 hipError_t stress(dk_ctx* c, const void* x, long ld, int n_s, const double* ds, double* kinetic,
                   double* nonlocal, void* ws);
 
-// nonlocal.hip
-hipError_t projector_group_lists(dk_ctx* c);
+// sweep.hip
+hipError_t build_sweep_tables(dk_ctx* c);
+void free_sweep_tables(dk_ctx* c);
 size_t nonlocal_ws_bytes(const dk_ctx* c, int n_s);
 // Y += alpha sum_p gamma_p chi_p (h^3 chi_p^T X) in two calls: the integrals
 // of X into ws, then the scatter into Y from ws.  subspace: the product only
@@ -192,19 +186,11 @@ size_t nonlocal_ws_bytes(const dk_ctx* c, int n_s);
 hipError_t nonlocal_integrals(dk_ctx* c, const void* x, long ld, int n_s, double alpha, void* ws,
                               bool subspace);
 hipError_t nonlocal_scatter(dk_ctx* c, void* y, long ld, int n_s, void* ws);
+
+// nonlocal.hip
 size_t projector_integrals_ws_bytes(const dk_ctx* c, int n_s, int m_rows);
 hipError_t projector_integrals(dk_ctx* c, const void* x, long ld, int n_s, const void* table,
                                int m_rows, double scale, double* out, void* ws);
-
-// gather.hip
-bool use_gather_chunks(const dk_ctx* c);
-hipError_t build_gather_chunks(dk_ctx* c);
-void free_gather_chunks(dk_ctx* c);
-size_t gather_chunks_ws_bytes(const dk_ctx* c, int n_s);
-hipError_t build_table_pieces(dk_ctx* c);
-hipError_t gather_chunks(dk_ctx* c, const void* x, long ld, int n_s, double scale,
-                         const double* rowscale, double* out64, float* out32, void* ws,
-                         bool two_piece = false);
 
 // linalg.hip
 size_t gram_ws_bytes(const dk_ctx* c, int n_s);

@@ -87,24 +87,6 @@ __global__ void build_tables_kernel(const double* __restrict__ pos, int n_atoms,
   }
 }
 
-// mask_t[(p/64) gblocks + gb] = 1 if any entry of projector p in the 64-point
-// block gb is nonzero (every writer stores 1); one wave per (projector,
-// block), lane i reading point 64 gb + i
-__global__ __launch_bounds__(256) void table_masks_kernel(const double* __restrict__ chi, long ng,
-                                                          int n_proj, long gblocks,
-                                                          uint8_t* __restrict__ mask_t) {
-  const int lane = threadIdx.x & 63;
-  const long total = gblocks * n_proj;
-  const long stride = ((long)gridDim.x * blockDim.x) >> 6;
-  for (long e = (blockIdx.x * (long)blockDim.x + threadIdx.x) >> 6; e < total; e += stride) {
-    const long gb = e % gblocks;
-    const int p = (int)(e / gblocks);
-    const long x = gb * 64 + lane;
-    const bool nz = x < ng && chi[(long)p * ng + x] != 0.0;
-    if (__any(nz) && lane == 0) mask_t[(long)(p / 64) * gblocks + gb] = 1;
-  }
-}
-
 // norms[p] = sum_x chi_p(x)^2, one block per projector
 __global__ __launch_bounds__(256) void table_norms_kernel(const double* __restrict__ chi, long ng,
                                                           double* __restrict__ norms) {
@@ -116,11 +98,6 @@ __global__ __launch_bounds__(256) void table_norms_kernel(const double* __restri
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
   __syncthreads();
   if (threadIdx.x == 0) norms[blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
-}
-
-__global__ void table_f32_kernel(const double* __restrict__ s, float* __restrict__ d, long n) {
-  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < n; e += (long)gridDim.x * blockDim.x)
-    d[e] = (float)s[e];
 }
 
 inline int blocks_for(long n) {
@@ -260,7 +237,7 @@ int model_functions(int n_channels, const int* l) {
   return f;
 }
 
-// Fills chi64 (and chi32 if present), the masks and the per-projector norms
+// Fills chi64 and the per-projector norms
 // (host) for the atoms at pos_dev.  Tables must already be allocated for
 // n_atoms * model_functions projectors.
 static ChannelSet channel_set(int n_channels, const int* l, const double* rc, double cutoff_rel) {
@@ -290,16 +267,8 @@ hipError_t build_projector_tables(dk_ctx* c, const double* pos_dev, int n_atoms,
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int n_proj = n_atoms * cs.per_atom;
-  const long gblocks = (ng + 63) / 64;
-  const int ptiles = (n_proj + 63) / 64;
-  if ((e = hipMemsetAsync(c->mask_t, 0, (size_t)ptiles * gblocks, c->stream)) != hipSuccess) return e;
-  hipLaunchKernelGGL(table_masks_kernel, dim3(blocks_for(gblocks * n_proj * 64)), dim3(256), 0,
-                     c->stream, c->chi64, ng, n_proj, gblocks, c->mask_t);
   hipLaunchKernelGGL(table_norms_kernel, dim3(n_proj), dim3(256), 0, c->stream, c->chi64, ng,
                      norms_dev);
-  if (c->chi32)
-    hipLaunchKernelGGL(table_f32_kernel, dim3(blocks_for(ng * n_proj)), dim3(256), 0, c->stream,
-                       c->chi64, c->chi32, ng * n_proj);
   return hipGetLastError();
 }
 

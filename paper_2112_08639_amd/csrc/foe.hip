@@ -17,7 +17,7 @@
 #include <cmath>
 
 #include "ctx.h"
-#include "gemm.h"
+#include "gemm_f64.h"
 
 namespace dk {
 
@@ -483,24 +483,16 @@ hipError_t foe_run(dk_ctx* c, const double* hs, int n_s, double n_e, double sigm
       const int k = built;
       const int cnt = (2 * k <= target) ? k : target - k;
       KTimer kt(c, DK_K_FOE_GEMM);
-      GemmArgs g;
+      NtArgs g;
       g.M = n_s; g.N = n_s; g.K = n_s;
-      g.A = stack + (long)k * nn; g.lda = n_s;         // T_k, m-contiguous (symmetric)
-      g.B = stack + nn; g.ldb = n_s;                    // T_i, i = 1..cnt
-      g.C = stack + (long)(k + 1) * nn; g.ldc = n_s;   // T_{k+i}
+      g.A = stack + (long)k * nn; g.lda = n_s;           // T_k
+      g.B = stack + nn; g.ldb = n_s;                     // T_i, i = 1..cnt
+      g.C = stack + (long)(k + 1) * nn; g.ldc = n_s;     // T_{k+i}
       g.Cin = stack + (long)(k - 1) * nn; g.ldcin = n_s; // T_{k-i}
       g.alpha = 2.0; g.beta = -1.0;
-      // every T_j is symmetric: upper tiles only, each mirrored into the lower
-      g.tile_sel = kUpperTiles;
-      g.mirror = 1;
       g.batch = cnt;
       g.bs_a = 0; g.bs_b = nn; g.bs_c = nn; g.bs_cin = -nn;
-      // 32x32 tiles keep every CU busy for small batches of subspaces up to
-      // ~1000 orbitals; 64x64 tiles once the batch alone gives ~1000 of them
-      const long tiles64 = (long)ceil_div(n_s, 64) * ceil_div(n_s, 64) * cnt;
-      hipError_t r = (n_s <= 1024 && tiles64 < 1024)
-          ? launch_gemm<kF64, double, double, false, true, kStore, double, 32>(g, c->stream)
-          : launch_gemm<kF64, double, double, false, true, kStore, double, 64>(g, c->stream);
+      const hipError_t r = symmetric_product(g, c->stream);
       if (r != hipSuccess) return r;
       built = k + cnt;
     }

@@ -6,6 +6,7 @@
 
 #include "ctx.h"
 #include "gemm.h"
+#include "gemm_f64.h"
 
 namespace dk {
 
@@ -192,44 +193,30 @@ hipError_t check_finite(dk_ctx* c, const double* p, long n) {
 
 // ----------------------------------------------------------------- Gram --
 
-// Split-K of the N_grid-long products X^T Y.  Up to 256 output tiles
-// (N_s <= 1024): about 4096 workgroups; beyond, about 32768 counting every
-// tile (half of them run for a Gram matrix), at most 128 splits.  Measured
-// (FP64 MFMA on FP32 X): 884736 x 4096, 617 ms with 1 split against 325 ms
-// with 8; 373248 x 2048, 54 ms with 4 against 34 ms with 32; at 110592 x 512
-// 128 splits instead of 64 cost more in partial traffic than they gain.
-static void plan_gram(GemmArgs& g) {
-  const long tiles = (long)ceil_div(g.M, 64) * ceil_div(g.N, 64);
-  plan_split_k(g, tiles <= 256 ? 4096 : 32768);
-  if (g.splits > 128) {
-    const long kblocks = (g.K + 63) / 64;
-    const long per = (kblocks + 127) / 128;
-    g.k_per_split = (int)(per * 64);
-    g.splits = (int)((kblocks + per - 1) / per);
-  }
-}
-
-// Beyond 256 tiles of 64 (N_s > 1024) the FP64 products X^T Y run 128 x 128
-// tiles (each wave 64 x 64: half the LDS reads per MFMA of the 64 x 64 tile,
-// which keeps four workgroups per CU LDS-bound).  At 884736 x 4096: the
-// projection 545 against 639 ms, split to about 2048 workgroups; the Gram
-// (upper tiles) 632 against 686 ms, split to about 8192 so that the last of
-// its rounds is short (at about 2048: 991 ms).  On the FP32 block of the mixed
-// path the 128 x 128 Gram ran slower (807 against 666 ms): it keeps 64 x 64.
-constexpr int kGramWideTile = 128;
-static bool gram_wide(int n_s) { return (long)ceil_div(n_s, 64) * ceil_div(n_s, 64) > 256; }
-static void plan_gram_wide(GemmArgs& g, bool upper) {
-  const long tm = ceil_div(g.M, kGramWideTile), tn = ceil_div(g.N, kGramWideTile);
-  const long active = upper ? (tm * (tm + 1)) / 2 : tm * tn;
+// Split-K of the N_grid-long FP64 products X^T Y: 64 x 64 tiles, four workgroups
+// per CU (LDS).  Taken: the number of splits with the least of (rounds of 1024
+// workgroups) x (K range of one) plus the traffic of the partials.
+constexpr int kGramTile = 64, kGramSlab = 16;
+static void plan_gram(NtArgs& g) {
+  const long tm = ceil_div(g.M, kGramTile), tn = ceil_div(g.N, kGramTile);
+  const long tiles = g.upper ? tm * (tm + 1) / 2 : tm * tn;
   const long kblocks = (g.K + 63) / 64;
-  // upper tiles: about 16 rounds of two workgroups per CU, so that the last
-  // round is a small part of the whole (at 3 rounds the tail cost 2x)
-  long want = (upper ? 8192 : 2048) / (active > 0 ? active : 1);
-  if (want < 1) want = 1;
-  if (want > kblocks) want = kblocks;
-  const long per = (kblocks + want - 1) / want;
-  g.k_per_split = (int)(per * 64);
-  g.splits = (int)((kblocks + per - 1) / per);
+  constexpr long kSlots = 1024;
+  // per 64 of K, one round of the chip: 1024 x 64^3 x 2 FLOP at 70 TFLOP/s, in us
+  constexpr double kBlockUs = 1024.0 * 64 * 64 * 64 * 2 / 70e6;
+  // a partial of one tile, written and read, at 4 TB/s
+  constexpr double kPartUs = 64.0 * 64 * 8 * 2 / 4e6;
+  double best = 0.0;
+  for (long s = 1; s <= 128 && s <= kblocks; ++s) {
+    const long per = (kblocks + s - 1) / s, splits = (kblocks + per - 1) / per;
+    const double us = (double)((tiles * splits + kSlots - 1) / kSlots) * per * kBlockUs +
+                      (double)(tiles * splits) * kPartUs;
+    if (s == 1 || us < best) {
+      best = us;
+      g.k_per_split = per * 64;
+      g.splits = (int)splits;
+    }
+  }
 }
 
 // The split-BF16 projection runs 128 x 128 tiles (four 64 x 64 sub-tiles per
@@ -252,22 +239,21 @@ static void plan_projection(GemmArgs& g) {
 }
 
 size_t gram_ws_bytes(const dk_ctx* c, int n_s) {
-  GemmArgs g;
-  g.M = n_s;
-  g.N = n_s;
-  g.K = (int)c->ngrid;
-  plan_gram(g);
-  size_t bytes = (size_t)g.splits * n_s * n_s * sizeof(double);
-  if (c->precision == DK_PREC_FP64 && gram_wide(n_s)) {
-    for (int upper = 0; upper < 2; ++upper) {
-      GemmArgs w = g;
-      plan_gram_wide(w, upper != 0);
-      const size_t wb = (size_t)w.splits * n_s * n_s * sizeof(double);
-      if (wb > bytes) bytes = wb;
-    }
+  size_t bytes = 0;
+  for (int upper = 0; upper < 2; ++upper) {
+    NtArgs g;
+    g.M = g.N = n_s;
+    g.K = c->ngrid;
+    g.upper = upper;
+    plan_gram(g);
+    const size_t b = (size_t)g.splits * n_s * n_s * sizeof(double);
+    if (b > bytes) bytes = b;
   }
   if (c->precision == DK_PREC_MIXED) {
-    GemmArgs p = g;
+    GemmArgs p;
+    p.M = n_s;
+    p.N = n_s;
+    p.K = (int)c->ngrid;
     plan_projection(p);
     const size_t pb = (size_t)p.splits * n_s * n_s * sizeof(float);
     if (pb > bytes) bytes = pb;
@@ -284,38 +270,40 @@ size_t gram_ws_bytes(const dk_ctx* c, int n_s) {
 hipError_t gram(dk_ctx* c, const void* x, const void* y, long ld, int n_s, bool symmetric_x,
                 double scale, double* out, void* ws, bool bf16x3, int kind) {
   KTimer kt(c, kind);
-  GemmArgs g;
-  g.M = n_s;
-  g.N = n_s;
-  g.K = (int)c->ngrid;
+  const dim3 rgrid(ceil_div(n_s, RT), ceil_div(n_s, RT));
+  hipError_t e;
+  if (c->precision == DK_PREC_MIXED && bf16x3) {
+    GemmArgs p;
+    p.M = n_s;
+    p.N = n_s;
+    p.K = (int)c->ngrid;
+    p.A = x;
+    p.lda = ld;
+    p.B = y;
+    p.ldb = ld;
+    p.C = ws;
+    p.tile_sel = symmetric_x ? kUpperTiles : kAllTiles;
+    plan_projection(p);
+    e = launch_gemm<kBF16X3S, float, float, true, true, kPartial, float, kProjTile, kProjTile, 32>(
+        p, c->stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(reduce_square_kernel<float>, rgrid, dim3(256), 0, c->stream,
+                       (const float*)ws, p.splits, n_s, scale, symmetric_x ? 1 : 0, out);
+    return hipGetLastError();
+  }
+  NtArgs g;
+  g.M = g.N = n_s;
+  g.K = c->ngrid;
   g.A = x;
   g.lda = ld;
   g.B = y;
   g.ldb = ld;
-  g.C = ws;
-  g.tile_sel = symmetric_x ? kUpperTiles : kAllTiles;
-  const dim3 rgrid(ceil_div(n_s, RT), ceil_div(n_s, RT));
-  hipError_t e;
-  if (c->precision == DK_PREC_MIXED && bf16x3) {
-    plan_projection(g);
-    e = launch_gemm<kBF16X3S, float, float, true, true, kPartial, float, kProjTile, kProjTile, 32>(
-        g, c->stream);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(reduce_square_kernel<float>, rgrid, dim3(256), 0, c->stream,
-                       (const float*)ws, g.splits, n_s, scale, symmetric_x ? 1 : 0, out);
-    return hipGetLastError();
-  }
-  if (gram_wide(n_s) && c->precision == DK_PREC_FP64) {
-    plan_gram_wide(g, symmetric_x);
-    e = launch_gemm<kF64, double, double, true, true, kPartial, double, kGramWideTile,
-                    kGramWideTile, 8>(g, c->stream);
-  } else {
-    plan_gram(g);
-    if (c->precision == DK_PREC_FP64)
-      e = launch_gemm<kF64, double, double, true, true, kPartial, double>(g, c->stream);
-    else
-      e = launch_gemm<kF64, float, float, true, true, kPartial, double>(g, c->stream);
-  }
+  g.C = (double*)ws;
+  g.upper = symmetric_x ? 1 : 0;
+  plan_gram(g);
+  e = c->precision == DK_PREC_FP64
+          ? launch_nt<double, double, true, kGramTile, kGramSlab, 4>(g, c->stream)
+          : launch_nt<float, float, true, kGramTile, kGramSlab, 4>(g, c->stream);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(reduce_square_kernel<double>, rgrid, dim3(256), 0, c->stream,
                      (const double*)ws, g.splits, n_s, scale, symmetric_x ? 1 : 0, out);
@@ -689,7 +677,7 @@ static hipError_t squaring_pair(dk_ctx* c, const double* hs, int n, double* M, d
     const int active = (done_m[0] ? 0 : 1) + (done_m[1] ? 0 : 1);
     double* P = (k & 1) ? Y : X;  // this step's input
     double* Q = (k & 1) ? X : Y;  // and output
-    GemmArgs g;
+    NtArgs g;
     g.M = n; g.N = n; g.K = n;
     g.A = P + first * nn; g.lda = n;
     g.B = P + first * nn; g.ldb = n;
@@ -699,14 +687,7 @@ static hipError_t squaring_pair(dk_ctx* c, const double* hs, int n, double* M, d
     squarings += active;
     g.bs_a = g.bs_b = g.bs_c = nn;
     // X_k is symmetric (a power of M): upper tiles only, mirrored
-    g.tile_sel = kUpperTiles;
-    g.mirror = 1;
-    // 32-deep K slabs: half the slab barriers of the 16-deep default for these
-    // small, latency-bound products (al32 bounds 0.73 -> 0.66 ms per step)
-    if (n <= 1024)
-      e = launch_gemm<kF64, double, double, false, true, kStore, double, 32, 32, 32>(g, c->stream);
-    else
-      e = launch_gemm<kF64, double, double, false, true, kStore, double, 64>(g, c->stream);
+    e = symmetric_product(g, c->stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(squaring_stats_kernel, dim3(blocks, active), dim3(256), 0, c->stream, M,
                        Q, n, part, first, est, SB_MAX_STEPS, k, alpha, cnt);

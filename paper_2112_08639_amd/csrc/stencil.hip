@@ -9,13 +9,16 @@
 // Y_{k-1} with Y_{k+1} point by point).  The nonlocal projector term is added
 // by nonlocal_scatter.
 //
-// Kernel layout.  A workgroup owns one column of the block, TY full x-rows of
+// Kernel layout.  All kernels stream planes; the first and general one, for rows of any
+// length: a workgroup owns one column of the block, TY full x-rows of
 // an xy-plane, and streams through a chunk of z-planes.  Each thread keeps the
 // 13 values of its points' z-columns in registers (a queue shifted once per
 // plane), so every value of Y_in is loaded from memory once per chunk plus a
 // 12-plane prologue.  The centre plane of the tile, with 6 periodic halo rows
 // above and below, is staged in LDS for the x and y neighbours; x wraps within
 // the row.
+#include <algorithm>
+#include <cmath>
 #include <utility>
 
 #include "ctx.h"
@@ -315,130 +318,8 @@ __global__ __launch_bounds__(MAXT) void stencil_plane_kernel(StencilArgs a) {
   }
 }
 
-// FP32 whole-plane variant for planes with 8 <= nx <= 64 and ny >= 6.  Rows
-// have a fixed pitch and the plane carries 6 periodic copies of rows above and
-// below it, so every LDS read of a thread is one base address plus a constant
-// offset, and the FP32 coefficients come converted from the host (scalar
-// operands).  That brings the kernel to 90 VGPRs: two plane workgroups share a
-// CU.  Per thread and plane the LDS reads are twelve 16-byte vectors for the y
-// neighbours and two 16-byte plus two 8-byte ones for x: the x window skips
-// the thread's own four values, which it holds in registers.  V_eff and
-// Y_{k-1} are loaded after the barrier; their latency is covered by the LDS
-// part and by the CU's other workgroup.
-constexpr int kPitch2 = 80;
-template <int MAXT>
-__global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(5)))
-void stencil_plane2_kernel(StencilArgs a) {
-  extern __shared__ unsigned char smem_raw[];
-  float* lds = reinterpret_cast<float*>(smem_raw);
-  const int nx = a.nx, ny = a.ny, nz = a.nz;
-  const int plane_lds = (ny + 12) * kPitch2;
-  const int pstride = nx * ny;
-  const int col = blockIdx.z;
-  const int z0 = blockIdx.y * a.zc;
-  const int z1 = min(nz, z0 + a.zc);
-  const int segs = nx / 4;
-  const int t = threadIdx.x;
-  const bool active = t < segs * ny;
-  const int y = active ? t / segs : 0;
-  const int x0 = active ? 4 * (t - y * segs) : 0;
-  const int off = x0 + nx * y;
-
-  const float* __restrict__ yin = reinterpret_cast<const float*>(a.yin) + (long)col * a.ld;
-  const float* __restrict__ yprev =
-      a.yprev ? reinterpret_cast<const float*>(a.yprev) + (long)col * a.ld : nullptr;
-  float* yout = reinterpret_cast<float*>(a.yout) + (long)col * a.ld;
-  const float* __restrict__ veff = reinterpret_cast<const float*>(a.veff);
-
-  const float* cx = a.fcx;
-  const float* cy = a.fcy;
-  const float* cz = a.fcz;
-  const float alpha = a.falpha, beta = a.fbeta, vshift = a.fshift;
-
-  // LDS row y + 6 holds plane row y; rows 0..5 and ny+6..ny+11 are periodic
-  // copies.  base: row y (six rows above the own row), x0 - kPad.
-  const int base = y * kPitch2 + x0;
-  const int own = base + 6 * kPitch2 + kPad;
-  const int copy_r = (x0 < kPad) ? own + nx : -1;
-  const int copy_l = (x0 >= nx - kPad) ? own - nx : -1;
-  const int copy_dn = (y < 6) ? own + ny * kPitch2 : -1;
-  const int copy_up = (y >= ny - 6) ? own - ny * kPitch2 : -1;
-
-  Vec4<float> q[13];
-  const Vec4<float> zero4 = {{0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-  for (int d = 0; d < 12; ++d) {
-    int zz = z0 - 6 + d;
-    zz = ((zz % nz) + nz) % nz;
-    q[d] = active ? ld4(yin + zz * pstride + off) : zero4;
-  }
-  int zn = z0 + 6; if (zn >= nz) zn -= nz;
-  Vec4<float> nxt = active ? ld4(yin + zn * pstride + off) : zero4;
-  int buf = 0;
-  for (int z = z0; z < z1; ++z) {
-    q[12] = nxt;
-    int zl = z + 7; if (zl >= nz) zl -= nz;
-    if (z + 1 < z1 && active) nxt = ld4(yin + zl * pstride + off);
-    const int g = z * pstride + off;
-    float* P = lds + buf * plane_lds;
-    if (active) {
-      st4(P + own, q[6]);
-      if (copy_r >= 0) st4(P + copy_r, q[6]);
-      if (copy_l >= 0) st4(P + copy_l, q[6]);
-      if (copy_dn >= 0) st4(P + copy_dn, q[6]);
-      if (copy_up >= 0) st4(P + copy_up, q[6]);
-    }
-    __syncthreads();
-    if (active) {
-      const Vec4<float> vv = ld4(veff + g);
-      const Vec4<float> pv = yprev ? ld4(yprev + g) : zero4;
-      const float* B = P + base;
-      float acc[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] = 0.f;
-      {
-        // x neighbours x0 - 6 .. x0 + 9 of the own row: two 8-byte and two
-        // 16-byte reads around the thread's own four values (in registers)
-        const float* R = B + 6 * kPitch2 + kPad;
-        const float2 l2 = *reinterpret_cast<const float2*>(R - 6);
-        const Vec4<float> l4 = ld4(R - 4);
-        const Vec4<float> r4 = ld4(R + 4);
-        const float2 r2 = *reinterpret_cast<const float2*>(R + 8);
-        float w[16];  // w[m]: the value at x0 - 6 + m
-        w[0] = l2.x; w[1] = l2.y;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { w[2 + j] = l4.v[j]; w[6 + j] = q[6].v[j]; w[10 + j] = r4.v[j]; }
-        w[14] = r2.x; w[15] = r2.y;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int k = 1; k <= 6; ++k)
-            acc[i] += cx[k] * pair_d2(w[6 + i + k], w[6 + i - k], q[6].v[i]);
-      }
-#pragma unroll
-      for (int k = 1; k <= 6; ++k) {
-        const Vec4<float> up = ld4(B + (6 + k) * kPitch2 + kPad);
-        const Vec4<float> dn = ld4(B + (6 - k) * kPitch2 + kPad);
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          acc[i] += cy[k] * pair_d2(up.v[i], dn.v[i], q[6].v[i]) +
-                    cz[k] * pair_d2(q[6 + k].v[i], q[6 - k].v[i], q[6].v[i]);
-      }
-      Vec4<float> out;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        out.v[i] = alpha * (acc[i] + (vv.v[i] - vshift) * q[6].v[i]) +
-                   (yprev ? beta * pv.v[i] : 0.f);
-      st4(yout + g, out);
-    }
-    buf ^= 1;
-#pragma unroll
-    for (int d = 0; d < 12; ++d) q[d] = q[d + 1];
-  }
-}
-
 // FP32 whole-plane variant with the x halo taken by DPP row rotations, for
-// nx = 16 P (P = 2 or 3), 6 <= ny <= 48 and nz >= 7.  Thread t owns the P
+// nx = 16 P with P = 3, 6 <= ny <= 48 and nz >= 7.  Thread t owns the P
 // consecutive points x0 = P (t % 16) .. x0 + P - 1 of row y = t / 16, so the
 // 16 lanes of a DPP row hold one whole x-row of the plane: the x neighbours
 // x0 - 6 .. x0 + P + 5 are the values of the lanes ceil(6/P) to either side,
@@ -481,10 +362,9 @@ __device__ __forceinline__ void x_window_all(const float (&own)[P], float (&w)[P
   (window_lane_dispatch<P, I - L>(own, w), ...);
 }
 
-template <int P>
 __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(6)))
 void stencil_dpp_kernel(StencilArgs a) {
-  static_assert(P == 2 || P == 3, "16 lanes of P points per row");
+  constexpr int P = 3;
   extern __shared__ unsigned char smem_raw[];
   float* lds = reinterpret_cast<float*>(smem_raw);
   const int nx = a.nx, ny = a.ny, nz = a.nz;  // nx = 16 P, blockDim = 16 ny
@@ -804,6 +684,251 @@ __global__ __launch_bounds__(MAXT) void stencil_slab_kernel(StencilArgs a) {
   }
 }
 
+// Slab kernel for rows of any length: one column of the block, a slab of TY rows and a
+// chunk of z-planes per workgroup.  A thread owns W consecutive points of a row (16
+// bytes), the last segment of a row only its first R = nx % W (R = 0: all W).  Loads of
+// that segment start at the last W points of the row, so that nothing past the row is
+// read, and are shifted into place; its LDS and memory writes are element by element.
+// All vectors need element alignment only, so nx, ld and the base may be anything.
+//
+// The z-queue lives in registers; the centre plane goes to one of two LDS buffers, rows
+// of constant pitch with six periodic copies at either end, six rows above and six below
+// (WHOLE: the slab is the plane and they are its own rows; otherwise they are read from
+// memory).  Every LDS read is one base and a constant offset.  Idle threads of the last
+// wave repeat thread 0 and write nothing, so no load is conditional.
+//
+// The bound is memory (three streams), closely followed by the VALU (18 neighbour pairs a
+// point, three operations each).  What the time above the floor goes to is latency: one
+// barrier per plane, and no prefetch beyond it, since at more than 128 VGPRs only 12 waves
+// run on a CU (V_eff and Y_{k-1} loaded above the barrier, or the queue kept two planes
+// long to halve its moves, spill and lose 20 to 60 %).  Measured against the kernels taken
+// before (time of one application, memory floor at 4.7 TB/s):
+//   FP32 72^3 x 2048    2.78 -> 2.38 ms (1.94)    FP32 45 x 40 x 54 x 203  215 -> 109 us (50)
+//   FP32 64^3 x 256      231 -> 180 us (170)      FP32 50^3 x 300          434 -> 163 us (95)
+//   FP64 48^3 x 512      430 -> 405 us (287)      FP64 71 x 67 x 70 x 150  750 -> 357 us (252)
+//   FP64 24^3 x 64      20.5 -> 9.8 us (4.5)      FP32 24^3 x 512           38 -> 29 us (18)
+// Rows that are no multiple of four run at 0.55 of the rate of those that are: 16-byte
+// loads off their alignment are split.  (A thread owning four rows at one x, all accesses
+// single elements, spilled: 255 us at 45 x 40 x 54 x 203.)
+// LDS pitch of a row: its length, kPad copies at either end, a multiple that leaves sixteen
+// waves of narrow planes room in LDS (nx <= 32: 48, else 96)
+constexpr int rows_pitch(int nx) { return nx <= 32 ? 48 : 96; }
+constexpr int kRowsMaxNx = 80;
+
+template <typename T, int W>
+__device__ __forceinline__ VecW<T, W> ldu(const T* p) {
+  typedef T vec __attribute__((ext_vector_type(W), aligned(sizeof(T))));
+  const vec u = *reinterpret_cast<const vec*>(p);
+  VecW<T, W> r;
+#pragma unroll
+  for (int i = 0; i < W; ++i) r.v[i] = u[i];
+  return r;
+}
+
+template <typename T, int W>
+__device__ __forceinline__ void stu(T* p, const VecW<T, W>& r) {
+  typedef T vec __attribute__((ext_vector_type(W), aligned(sizeof(T))));
+  vec u;
+#pragma unroll
+  for (int i = 0; i < W; ++i) u[i] = r.v[i];
+  *reinterpret_cast<vec*>(p) = u;
+}
+
+template <typename T, int W, int R, bool WHOLE, int PITCH>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4)))
+void stencil_rows_kernel(StencilArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  T* lds = reinterpret_cast<T*>(smem_raw);
+  const int nx = a.nx, ny = a.ny, nz = a.nz;
+  const int y0 = WHOLE ? 0 : blockIdx.x * a.ty_tile;
+  const int ty = WHOLE ? ny : min(a.ty_tile, ny - y0);
+  const int plane_lds = (a.ty_tile + 12) * PITCH;
+  const int pstride = nx * ny;
+  const int col = blockIdx.z;
+  const int z0 = blockIdx.y * a.zc;
+  const int z1 = min(nz, z0 + a.zc);
+  const int segs = (nx + W - 1) / W;
+  const int t = threadIdx.x;
+  const bool active = t < segs * ty;
+  const int ly = active ? t / segs : 0;
+  const int x0 = active ? W * (t - ly * segs) : 0;
+  const bool last = R != 0 && x0 + W > nx;
+  const int off = x0 + nx * (y0 + ly);
+  // byte offsets within a plane: of the segment, and of where its vector loads start
+  const unsigned ooff = off * (unsigned)sizeof(T);
+  const unsigned loff = (last ? off - (W - R) : off) * (unsigned)sizeof(T);
+
+  const T* __restrict__ yin = reinterpret_cast<const T*>(a.yin) + (long)col * a.ld;
+  const T* __restrict__ yprev =
+      a.yprev ? reinterpret_cast<const T*>(a.yprev) + (long)col * a.ld : nullptr;
+  T* yout = reinterpret_cast<T*>(a.yout) + (long)col * a.ld;
+  const T* __restrict__ veff = reinterpret_cast<const T*>(a.veff);
+  auto cx = [&](int k) -> T { if constexpr (sizeof(T) == 4) return a.fcx[k]; else return a.cx[k]; };
+  auto cy = [&](int k) -> T { if constexpr (sizeof(T) == 4) return a.fcy[k]; else return a.cy[k]; };
+  auto cz = [&](int k) -> T { if constexpr (sizeof(T) == 4) return a.fcz[k]; else return a.cz[k]; };
+  const T alpha = (T)a.alpha, beta = (T)a.beta, vshift = (T)a.shift;
+
+  auto load = [&](const T* base, int z, unsigned o, bool shifted) {
+    VecW<T, W> v = ldu<T, W>(
+        reinterpret_cast<const T*>(reinterpret_cast<const char*>(base + (long)z * pstride) + o));
+    if constexpr (R != 0) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) v.v[i] = shifted ? v.v[i + W - R] : v.v[i];
+    }
+    return v;
+  };
+  // a segment starting at x of the LDS row at `row`: itself and, at the ends of the row,
+  // its periodic copies
+  auto put = [&](T* row, int x, bool part, const VecW<T, W>& v, bool copies) {
+    T* o = row + kPad + x;
+    if (!part) stw<T, W>(o, v);
+    if constexpr (R != 0) {
+      if (part)
+#pragma unroll
+        for (int i = 0; i < R; ++i) o[i] = v.v[i];
+    }
+    if (!copies) return;
+    if (x < kPad) {
+      if constexpr (R == 0) stw<T, W>(o + nx, v);
+      else
+#pragma unroll
+        for (int i = 0; i < W; ++i) o[nx + i] = v.v[i];
+    }
+    if (x + W > nx - kFdRadius) {
+      if constexpr (R == 0) stw<T, W>(o - nx, v);
+      else
+#pragma unroll
+        for (int i = 0; i < W; ++i)
+          if (x + i < nx && x + i >= nx - kPad) o[i - nx] = v.v[i];
+    }
+  };
+
+  // halo rows from memory, one segment per thread (slabs have at least 12 rows): row
+  // h_row of the slab, segment at h_x
+  const int halo_items = 12 * segs;
+  int h_row = 0, h_x = 0;
+  unsigned h_off = 0;
+  bool h_part = false;
+  if constexpr (!WHOLE) {
+    const int e = min(t, halo_items - 1), hr = e / segs;
+    h_x = W * (e - hr * segs);
+    h_part = R != 0 && h_x + W > nx;
+    h_row = hr < 6 ? hr - 6 : ty + hr - 6;
+    int gy = y0 + h_row;
+    if (gy < 0) gy += ny;
+    if (gy >= ny) gy -= ny;
+    h_off = (unsigned)sizeof(T) * (nx * gy + (h_part ? nx - W : h_x));
+  }
+
+  const int base = ly * PITCH + x0;
+  VecW<T, W> q[13];
+#pragma unroll
+  for (int d = 0; d < 12; ++d) {
+    int zz = z0 - 6 + d;
+    if (zz < 0) zz += nz;
+    if (zz >= nz) zz -= nz;
+    q[d] = load(yin, zz, loff, last);
+  }
+  VecW<T, W> hv;
+  if constexpr (!WHOLE) hv = load(yin, z0, h_off, h_part);
+  int buf = 0;
+  for (int z = z0; z < z1; ++z) {
+    int zl = z + 6;
+    if (zl >= nz) zl -= nz;
+    q[12] = load(yin, zl, loff, last);
+    T* P = lds + buf * plane_lds;
+    if (active) {
+      put(P + (ly + 6) * PITCH, x0, last, q[6], true);
+      if constexpr (WHOLE) {
+        if (ly < 6) put(P + (ly + 6 + ny) * PITCH, x0, last, q[6], false);
+        if (ly >= ny - 6) put(P + (ly + 6 - ny) * PITCH, x0, last, q[6], false);
+      }
+    }
+    if constexpr (!WHOLE) {
+      if (t < halo_items) put(P + (h_row + 6) * PITCH, h_x, h_part, hv, false);
+    }
+    __syncthreads();
+    const T* B = P + base;
+    T acc[W];
+#pragma unroll
+    for (int i = 0; i < W; ++i) acc[i] = (T)0;
+    {
+      // x neighbours x0 - 6 .. x0 + W + 5, the own W from registers
+      const T* X = B + 6 * PITCH + kPad;
+      T w[W + 12];
+#pragma unroll
+      for (int i = 0; i < W; ++i) w[6 + i] = q[6].v[i];
+      if constexpr (W == 2) {
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+          const VecW<T, 2> l = ldw<T, 2>(X - 6 + 2 * s);
+          const VecW<T, 2> r = ldw<T, 2>(X + 2 + 2 * s);
+          w[2 * s] = l.v[0]; w[2 * s + 1] = l.v[1];
+          w[8 + 2 * s] = r.v[0]; w[9 + 2 * s] = r.v[1];
+        }
+      } else {
+        const VecW<T, 2> l2 = ldw<T, 2>(X - 6), r2 = ldw<T, 2>(X + 8);
+        const VecW<T, 4> l4 = ldw<T, 4>(X - 4), r4 = ldw<T, 4>(X + 4);
+        w[0] = l2.v[0]; w[1] = l2.v[1];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { w[2 + j] = l4.v[j]; w[10 + j] = r4.v[j]; }
+        w[14] = r2.v[0]; w[15] = r2.v[1];
+      }
+      // in the row's last segment the points right of the row's end are its periodic
+      // copies, not the (meaningless) rest of the own vector
+      if constexpr (R != 0) {
+        if (last) {
+#pragma unroll
+          for (int i = R; i < W; ++i) w[6 + i] = X[i];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < W; ++i)
+#pragma unroll
+        for (int k = 1; k <= kFdRadius; ++k)
+          acc[i] += cx(k) * pair_d2(w[6 + i + k], w[6 + i - k], q[6].v[i]);
+    }
+    // (kept below the x part: loaded above it they cost registers that the occupancy needs)
+    __builtin_amdgcn_sched_barrier(0);
+    const VecW<T, W> vv = load(veff, z, loff, last);
+    VecW<T, W> pv;
+    if (yprev) {
+      pv = load(yprev, z, loff, last);
+    } else {
+#pragma unroll
+      for (int i = 0; i < W; ++i) pv.v[i] = (T)0;
+    }
+#pragma unroll
+    for (int k = 1; k <= kFdRadius; ++k) {
+      const VecW<T, W> up = ldw<T, W>(B + (6 + k) * PITCH + kPad);
+      const VecW<T, W> dn = ldw<T, W>(B + (6 - k) * PITCH + kPad);
+#pragma unroll
+      for (int i = 0; i < W; ++i)
+        acc[i] += cy(k) * pair_d2(up.v[i], dn.v[i], q[6].v[i]) +
+                  cz(k) * pair_d2(q[6 + k].v[i], q[6 - k].v[i], q[6].v[i]);
+    }
+    VecW<T, W> out;
+#pragma unroll
+    for (int i = 0; i < W; ++i)
+      out.v[i] = alpha * (acc[i] + (vv.v[i] - vshift) * q[6].v[i]) +
+                 (yprev ? beta * pv.v[i] : (T)0);
+    T* o = reinterpret_cast<T*>(reinterpret_cast<char*>(yout + (long)z * pstride) + ooff);
+    if (active && !last) stu<T, W>(o, out);
+    if constexpr (R != 0) {
+      if (last)
+#pragma unroll
+        for (int i = 0; i < R; ++i) o[i] = out.v[i];
+    }
+    if constexpr (!WHOLE) {
+      const int zh = min(z + 1, nz - 1);
+      hv = load(yin, zh, h_off, h_part);
+    }
+    buf ^= 1;
+#pragma unroll
+    for (int d = 0; d < 12; ++d) q[d] = q[d + 1];
+  }
+}
+
 static void fill_coeffs(const dk_ctx* c, StencilArgs& a) {
   // twelfth-order central second-derivative weights (closed form of the
   // order-12 Lagrange stencil): w_0 = -5369/1800, w_k = 2(-1)^{k+1}(6!)^2/(k^2(6-k)!(6+k)!)
@@ -825,6 +950,82 @@ static void fill_coeffs(const dk_ctx* c, StencilArgs& a) {
   a.fbeta = (float)a.beta;
   a.fdshift = (float)(a.diag - a.shift);
   a.fshift = (float)a.shift;
+}
+
+// How the rows kernel cuts a block: slabs of equal height (of at least 12 rows, so that a
+// thread has one halo segment) and z-chunks.  At most 16 waves run on a CU (104 to 125
+// VGPRs), fewer where LDS or the size of a workgroup allows fewer.  The model of a cut:
+// a workgroup costs its waves (partly: its points) x (planes + prologue), more for halo
+// rows; m of them on a CU cost m (1 + share / m) of one, the share being what a lone
+// workgroup loses at its barriers, more while wave slots are idle; and rounds of them
+// follow each other, the last one partly filled.  The weights are fitted to the times of
+// all cuts of 31 shapes in FP32 and 10 in FP64 (16^3 x 40 to 72^3 x 1024): the chosen
+// cut is within 2 % of the best on average, 9 % at most.
+struct RowsWeights { double waves, prologue, halo, whole, share, idle, tail; };
+constexpr RowsWeights kRows32 = {0.37, 1.5, 0.12, 0.1, 0.75, 0.15, 0.33};
+constexpr RowsWeights kRows64 = {0.6, 2.3, 0.2, 0.08, 0.0, 0.85, 0.2};
+static size_t rows_lds_bytes(int nx, int ty, size_t elem) {
+  return 2 * (size_t)(ty + 12) * rows_pitch(nx) * elem;
+}
+
+struct RowsPlan { int slabs = 0, ty = 0, zc = 0, chunks = 0, threads = 0; };
+static RowsPlan plan_rows(int nx, int ny, int nz, int n_s, int W) {
+  const RowsWeights& w = W == 4 ? kRows32 : kRows64;
+  RowsPlan best;
+  double least = 0.0;
+  const int segs = ceil_div(nx, W);
+  for (int slabs = 1; slabs <= ny; ++slabs) {
+    const int ty = ceil_div(ny, slabs);
+    if (slabs > 1 && ty < 12) break;
+    if (ceil_div(ny, ty) != slabs) continue;
+    const int threads = (ty * segs + 63) / 64 * 64;
+    if (threads > 1024) continue;
+    const size_t lds = rows_lds_bytes(nx, ty, 16 / W);
+    if (lds > 160 * 1024) continue;
+    const int waves = threads / 64;
+    const int conc = std::max(1, std::min(16 / waves, (int)(160 * 1024 / lds)));
+    for (int z = 1; z <= std::max(1, nz / 4); ++z) {
+      const int zc = ceil_div(nz, z), chunks = ceil_div(nz, zc);
+      if (chunks != z) continue;
+      const double per = (w.waves * waves + (1.0 - w.waves) * ty * segs / 64.0) *
+                         (zc + w.prologue) * (1.0 + (slabs == 1 ? w.whole : w.halo * 12 / ty));
+      const double n = (double)slabs * chunks * n_s / 256;  // workgroups per CU
+      auto round = [&](double m) {
+        return (1.0 + w.idle * std::max(0.0, 1.0 - m * waves / 16)) * (m + w.share) * per;
+      };
+      const double full = std::floor(n / conc), rest = n - full * conc;
+      double t = full * round(conc);
+      if (rest > 1e-9) {
+        const double part = round(std::ceil(rest));
+        t += full > 0.0 ? w.tail * round(conc) * rest / conc + (1.0 - w.tail) * part : part;
+      }
+      if (best.slabs == 0 || t < least) {
+        least = t;
+        best = {slabs, ty, zc, chunks, threads};
+      }
+    }
+  }
+  return best;
+}
+
+template <typename T, int W, int R>
+static hipError_t launch_rows(StencilArgs a, const RowsPlan& p, int n_s, hipStream_t st) {
+  a.ty_tile = p.ty;
+  a.zc = p.zc;
+  const size_t smem = rows_lds_bytes(a.nx, p.ty, sizeof(T));
+  const bool narrow = rows_pitch(a.nx) == 48;
+  const auto kernel =
+      p.slabs == 1 ? (narrow ? stencil_rows_kernel<T, W, R, true, 48>
+                             : stencil_rows_kernel<T, W, R, true, 96>)
+                   : (narrow ? stencil_rows_kernel<T, W, R, false, 48>
+                             : stencil_rows_kernel<T, W, R, false, 96>);
+  if (smem > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute((const void*)kernel,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kernel, dim3(p.slabs, p.chunks, n_s), dim3(p.threads), smem, st, a);
+  return hipGetLastError();
 }
 
 template <typename T, int PPT>
@@ -865,9 +1066,43 @@ hipError_t stencil_step(dk_ctx* c, const void* yin, const void* yprev, void* you
   a.veff = f64 ? (const void*)c->veff64 : (const void*)c->veff32;
   KTimer kt(c, DK_K_STENCIL);
   const long plane = (long)c->nx * c->ny;
-  // whole-plane kernel: FP32 only (the FP64 queue of 4-wide vectors costs
-  // ~180 VGPRs and ran slower than the row-tile kernel)
-  if (!f64 && c->nx % 4 == 0 && c->nx >= kPad && plane <= 4096 && (ld % 4) == 0) {
+  // nx = 48 in FP32: one x-row per DPP row of 16 lanes, a whole plane per workgroup, two
+  // workgroups per CU.  Where such workgroups fill the chip (to 95 %) it is even with or
+  // ahead of the rows kernel (48^3 x 512: 188 against 191 us), elsewhere behind (48 x 40 x
+  // 54 x 203: 71 against 63 us)
+  if (!f64 && c->nx == 48 && c->ny >= 6 && c->ny <= 48 && ld % 4 == 0) {
+    int zch = ceil_div(512, (long)n_s);
+    zch = std::max(1, std::min(zch, c->nz / 12));
+    const int zc = ceil_div(c->nz, zch);
+    zch = ceil_div(c->nz, zc);
+    const long wgs = (long)n_s * zch, rounds = (wgs + 511) / 512;
+    if (wgs >= 0.95 * 512 * rounds) {
+      a.zc = zc;
+      const size_t smem = 2 * (size_t)(c->ny + 12) * c->nx * sizeof(float);
+      hipLaunchKernelGGL(stencil_dpp_kernel, dim3(1, zch, n_s), dim3(16 * c->ny), smem, c->stream,
+                         a);
+      return hipGetLastError();
+    }
+  }
+  if (c->nx <= kRowsMaxNx) {
+    const int W = f64 ? 2 : 4;
+    const RowsPlan p = plan_rows(c->nx, c->ny, c->nz, n_s, W);
+    if (p.slabs > 0) {
+      const int R = c->nx % W;
+      if (f64)
+        return R == 0 ? launch_rows<double, 2, 0>(a, p, n_s, c->stream)
+                      : launch_rows<double, 2, 1>(a, p, n_s, c->stream);
+      switch (R) {
+        case 0: return launch_rows<float, 4, 0>(a, p, n_s, c->stream);
+        case 1: return launch_rows<float, 4, 1>(a, p, n_s, c->stream);
+        case 2: return launch_rows<float, 4, 2>(a, p, n_s, c->stream);
+        default: return launch_rows<float, 4, 3>(a, p, n_s, c->stream);
+      }
+    }
+  }
+  // longer rows: a whole FP32 plane of up to 4096 points in one workgroup (the FP64 queue
+  // of 4-wide vectors costs ~180 VGPRs and ran slower than the row-tile kernel)
+  if (!f64 && c->nx % 4 == 0 && plane <= 4096 && ld % 4 == 0) {
     // whole-plane workgroups: one per column and z-chunk
     const int threads = ((int)(plane / 4) + 63) / 64 * 64;
     // z-chunks only when there are too few columns to fill the GPU: every
@@ -878,26 +1113,8 @@ hipError_t stencil_step(dk_ctx* c, const void* yin, const void* yprev, void* you
     if (zch < 1) zch = 1;
     a.zc = ceil_div(c->nz, zch);
     zch = ceil_div(c->nz, a.zc);
-    const size_t smem = 2 * (size_t)c->ny * (c->nx + 2 * kPad) * (f64 ? 8 : 4);
+    const size_t smem = 2 * (size_t)c->ny * (c->nx + 2 * kPad) * sizeof(float);
     dim3 grid(1, zch, n_s);
-    // nx = 32 or 48: one x-row per DPP row of 16 lanes (P = 4 needs more
-    // registers than two workgroups per CU allow)
-    const int P = c->nx / 16;
-    if (c->nx % 16 == 0 && (P == 2 || P == 3) && c->ny >= 6 && c->ny <= 48 && c->nz >= 7) {
-      const size_t smemd = 2 * (size_t)(c->ny + 12) * c->nx * sizeof(float);
-      const dim3 blk(16 * c->ny);
-      if (P == 2)
-        hipLaunchKernelGGL((stencil_dpp_kernel<2>), grid, blk, smemd, c->stream, a);
-      else
-        hipLaunchKernelGGL((stencil_dpp_kernel<3>), grid, blk, smemd, c->stream, a);
-      return hipGetLastError();
-    }
-    const size_t smem2 = 2 * (size_t)(c->ny + 12) * kPitch2 * sizeof(float);
-    if (c->nx >= kPad && c->nx + 2 * kPad <= kPitch2 && c->ny >= 6 && threads <= 640 &&
-        smem2 <= 64 * 1024) {
-      hipLaunchKernelGGL((stencil_plane2_kernel<640>), grid, dim3(threads), smem2, c->stream, a);
-      return hipGetLastError();
-    }
     if (smem <= 160 * 1024) {
       if (!(c->lds_attr_done & kAttrPlane)) {
         hipError_t e = hipFuncSetAttribute((const void*)stencil_plane_kernel<float, 640>,
@@ -915,9 +1132,8 @@ hipError_t stencil_step(dk_ctx* c, const void* yin, const void* yprev, void* you
       return hipGetLastError();
     }
   }
-  // slab kernel: FP32 planes larger than one workgroup (4-point vectors), and
-  // every FP64 plane (2-point vectors: the FP64 whole-plane form needs too many
-  // registers)
+  // longer rows, slab kernel: FP32 planes larger than one workgroup (4-point vectors),
+  // and FP64 planes (2-point vectors: the FP64 whole-plane form needs too many registers)
   {
     const int W = f64 ? 2 : 4;
     if (c->nx % W == 0 && (ld % W) == 0 && (f64 || plane > 4096) && c->nx <= W * 1024 / 7 &&

@@ -56,97 +56,227 @@ __global__ __launch_bounds__(256) void reduce_square_kernel(const PT* __restrict
   }
 }
 
-// Factor the NB x NB diagonal block at (k0, k0) of the lower-triangular
-// working matrix: A_kk = L L^T, then Linv = L^{-1}.  L goes back into the
-// lower triangle of g, Linv into the same block of linv.
-// A pivot below 1e-14 of the original diagonal entry (diag) is treated as
-// singular: X is then rank-deficient to working precision.
-// One workgroup of 256 threads with the block in LDS; thread t owns the
-// entries e = t + 256 q (q < 4) at row e % NB, column e / NB.  Both sweeps are
-// right-looking with one barrier per step:
-//   Cholesky step k: with d_k = a_kk, a_ij -= a_ik a_jk / d_k for k < j <= i
-//   (the columns are scaled by 1/sqrt(d_k) afterwards);
-//   inverse step i: z_jc -= l_ji z_ic / l_ii for j > i, c <= i, starting from
-//   Z = I (the rows are scaled by 1/l_ii afterwards).
-__global__ __launch_bounds__(256) void potrf_diag_kernel(double* g, int n, int k0, double* linv,
-                                                         const double* diag, unsigned* err) {
-  static_assert(NB == 32, "four entries of the 32 x 32 block per thread");
-  __shared__ double A[NB][NB + 1];
-  __shared__ double Z[NB][NB + 1];
-  __shared__ double dinv[NB];  // 1 / d_k, then 1 / l_kk
-  const int t = threadIdx.x;
-  const int nb = min(NB, n - k0);
-  int ri[4], cj[4];
+// Inverse Cholesky factor Z = L^{-1} of a symmetric positive definite G, NB columns a
+// step, by elimination on [G; I] (right-looking): with Z_k the inverse of the factor of
+// the current diagonal block,
+//   P_a   = G_ak Z_k^T                 for every block row a (L_ak below the diagonal)
+//   G_ab -= P_a P_b^T                  for a >= b > k   (trailing update)
+//   W_ab -= P_a P_b^T                  for a <= k < b   (forward substitution of I, W = Z^T)
+// where the row a = k of the second form starts from I (P_k = Z_k^T, W_kb = 0).  The
+// strictly upper blocks of G hold W: the lower triangle of G and the upper one of W never
+// meet, operands of all rows stand in block column k, and row k of Z is P_a^T, a < k.
+// The chain of steps is what takes the time (n = 512: 16 of them), so a step is one
+// launch: each workgroup forms the two P it needs itself (two 32^3 products, 0.5 us)
+// rather than wait for a panel launch, and the one with the next diagonal block
+// factors it at once.  Measured, factor and inverse: n = 512 740 -> 240 us, n = 2048
+// 4.8 -> 1.2 ms (before: a launch each for diagonal block, panel and trailing update, then
+// two per block row of the inverse); a step is 14 us at n = 512, most of it the
+// diagonal block's chain, and 18 us on average at n = 2048.
+typedef double f64x2_c __attribute__((ext_vector_type(2)));
+constexpr int CP = NB + 2;  // pitch of a block in LDS: rows four banks apart
+
+// 1 / sqrt(d) for d > 0: the hardware estimate and two Newton steps in residual form
+__device__ __forceinline__ double rsqrt_f64(double d) {
+  double y = __builtin_amdgcn_rsq(d);
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int e = t + 256 * q;
-    ri[q] = e & (NB - 1);
-    cj[q] = e >> 5;
-    const int i = ri[q], j = cj[q];
-    A[i][j] = (i < nb && j < nb) ? g[(k0 + i) + (long)(k0 + j) * n] : (i == j ? 1.0 : 0.0);
-    Z[i][j] = (i == j) ? 1.0 : 0.0;
+  for (int i = 0; i < 2; ++i) {
+    const double e = __builtin_fma(-d * y, y, 1.0);
+    y = __builtin_fma(0.5 * y, e, y);
   }
-  // lanes 0..31 of every wave hold the original diagonal entries of rows 0..31
-  const int lane = t & 63;
-  const double dref = (lane < nb) ? diag[k0 + lane] : 1.0;
-  __syncthreads();
+  return y;
+}
+
+// D = X Y^T of two 32 x 32 blocks in LDS ([row][k]); wave w computes the quadrant rows
+// 16 (w & 1), columns 16 (w >> 1): register q of lane l is D[l / 16 + 4 q][l % 16].
+__device__ __forceinline__ f64x4 block_nt(const double* X, const double* Y, int wave, int lane) {
+  const double* x = X + (16 * (wave & 1) + (lane & 15)) * CP + 4 * (lane >> 4);
+  const double* y = Y + (16 * (wave >> 1) + (lane & 15)) * CP + 4 * (lane >> 4);
+  f64x4 d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int k = 0; k < NB; k += 16)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const f64x2_c a = *reinterpret_cast<const f64x2_c*>(x + k + 2 * h);
+      const f64x2_c b = *reinterpret_cast<const f64x2_c*>(y + k + 2 * h);
+      d = mfma_f64(a[0], b[0], d);
+      d = mfma_f64(a[1], b[1], d);
+    }
+  return d;
+}
+
+// Factor the NB x NB block A (LDS, [row][col], lower triangle) = L L^T and leave L^{-1}
+// in Zi ([row][col]); one wave.  Lane r < 32 holds row r of A, lane 32 + r row r of I, and
+// the columns are eliminated in registers: the same operations that turn A into L turn
+// I into L^{-T}.  (The 32 steps are a serial chain of a reciprocal root and one column;
+// with the block in LDS, a barrier per step and a separate inverse: 22.5 us.)  A pivot
+// below 1e-14 of the original diagonal entry dref (lane r: of row r) is taken as
+// singular: X is then rank-deficient to working precision.
+__device__ void factor_block(const double* A, double* Zi, double dref, int lane, unsigned* err) {
+  double a[NB];
+  const int r = lane & (NB - 1);
+#pragma unroll
+  for (int c = 0; c < NB; ++c) a[c] = lane < NB ? A[r * CP + c] : (r == c ? 1.0 : 0.0);
+  auto lane_value = [](double v, int l) {
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
+    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
+    return __hiloint2double(hi, lo);
+  };
+  bool bad = false;
+#pragma unroll
   for (int k = 0; k < NB; ++k) {
-    double d = A[k][k];
-    const double ref = __shfl(dref, k);
-    if (!(d > 1e-14 * ref) || !isfinite(d)) {
-      if (t == 0) atomicOr(err, kErrNotSpd);
+    double d = lane_value(a[k], k);
+    if (!(d > 1e-14 * lane_value(dref, k)) || !isfinite(d)) {
+      bad = true;
       d = 1.0;
     }
-    const double id = 1.0 / d;
-    if (t == 0) dinv[k] = id;
+    const double l = a[k] * rsqrt_f64(d);
+    a[k] = l;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int i = ri[q], j = cj[q];
-      if (j > k && i >= j) A[i][j] -= A[i][k] * A[j][k] * id;
-    }
-    __syncthreads();
+    for (int c = k + 1; c < NB; ++c) a[c] = __builtin_fma(-l, lane_value(l, c), a[c]);
   }
-  // L: column k scaled by 1/sqrt(d_k) below the diagonal, l_kk = sqrt(d_k)
-  double lval[4];
+  if (bad && lane == 0) atomicOr(err, kErrNotSpd);
+  if (lane >= NB) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int i = ri[q], j = cj[q];
-    const double s = sqrt(dinv[j]);
-    lval[q] = (i > j) ? A[i][j] * s : ((i == j) ? 1.0 / s : 0.0);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < 4; ++q) A[ri[q]][cj[q]] = lval[q];
-  if (t < NB) dinv[t] = sqrt(dinv[t]);  // 1 / l_tt = 1 / sqrt(d_t)
-  __syncthreads();
-  for (int i = 0; i < NB; ++i) {
-    const double il = dinv[i];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int j = ri[q], c = cj[q];
-      if (j > i && c <= i) Z[j][c] -= A[j][i] * Z[i][c] * il;
-    }
-    __syncthreads();
-  }
-  // write L (zeros above the diagonal) and L^{-1} (rows scaled by 1/l_ii)
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int i = ri[q], j = cj[q];
-    if (i < nb && j < nb) {
-      g[(k0 + i) + (long)(k0 + j) * n] = (i >= j) ? A[i][j] : 0.0;
-      linv[(k0 + i) + (long)(k0 + j) * n] = (i >= j) ? Z[i][j] * dinv[i] : 0.0;
-    }
+    for (int c = 0; c < NB; ++c) Zi[c * CP + r] = c >= r ? a[c] : 0.0;
   }
 }
 
-__global__ void diag_kernel(const double* __restrict__ g, int n, double* __restrict__ d) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    d[i] = g[i + (long)i * n];
+// block (row0.., col0..) of the column-major n x n matrix m into LDS as [row][col]; rows
+// and columns past n: of the identity (pad) or zero
+__device__ __forceinline__ void load_block(const double* m, int n, int row0, int col0, bool pad,
+                                           double* s, int t) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = t & 31, c = (t >> 5) + 8 * q;
+    const bool in = row0 + r < n && col0 + c < n;
+    const double v = m[min(row0 + r, n - 1) + (long)min(col0 + c, n - 1) * n];
+    s[r * CP + c] = in ? v : (pad && r == c ? 1.0 : 0.0);
+  }
 }
 
-__global__ void zero_kernel(double* p, long n) {
-  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < n; e += (long)gridDim.x * blockDim.x)
-    p[e] = 0.0;
+// linv block k (on the diagonal) from LDS
+__device__ __forceinline__ void store_diag(double* linv, int n, int k, const double* Zi, int t) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = t & 31, c = (t >> 5) + 8 * q;
+    if (k * NB + r < n && k * NB + c < n)
+      linv[(k * NB + r) + (long)(k * NB + c) * n] = Zi[r * CP + c];
+  }
+}
+
+// diag = diagonal of g; linv = 0 outside its first diagonal block, which the first
+// workgroup factors
+__global__ __launch_bounds__(256) void chol_start_kernel(const double* __restrict__ g, int n,
+                                                         double* __restrict__ linv,
+                                                         double* __restrict__ diag, unsigned* err) {
+  __shared__ __attribute__((aligned(16))) double A[NB * CP];
+  __shared__ __attribute__((aligned(16))) double Zi[NB * CP];
+  const int t = threadIdx.x;
+  if (blockIdx.x > 0) {
+    const long nn = (long)n * n, step = (long)(gridDim.x - 1) * 256;
+    for (long e = (blockIdx.x - 1) * 256L + t; e < nn; e += step) {
+      const int i = (int)(e % n), j = (int)(e / n);
+      if (i >= NB || j >= NB) linv[e] = 0.0;
+      if (i == j) diag[i] = g[e];
+    }
+    return;
+  }
+  load_block(g, n, 0, 0, true, A, t);
+  __syncthreads();
+  if (t < 64) {
+    const int r = t & 31;
+    factor_block(A, Zi, r < n ? g[r + (long)r * n] : 1.0, t, err);
+  }
+  __syncthreads();
+  store_diag(linv, n, 0, Zi, t);
+}
+
+// Step k.  Workgroup (a, b), b > k: tile (a, b) of W (a <= k) or, as (b, a) with a > k,
+// of G; the last step has no such tiles and writes row k of Z only.
+__global__ __launch_bounds__(256) void chol_step_kernel(double* __restrict__ g, int n, int k,
+                                                        double* __restrict__ linv,
+                                                        const double* __restrict__ diag,
+                                                        unsigned* err) {
+  __shared__ __attribute__((aligned(16))) double Zk[NB * CP];
+  __shared__ __attribute__((aligned(16))) double Pa[NB * CP];
+  __shared__ __attribute__((aligned(16))) double Pb[NB * CP];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int nb = (n + NB - 1) / NB;
+  const bool final_row = k == nb - 1;
+  // tiles in order of b, then a = 0 .. b, but first the one to be factored, (k + 1, k + 1)
+  int a, b = k;
+  if (final_row) {
+    a = blockIdx.x;
+  } else {
+    const int x = blockIdx.x;
+    const long id = (long)(k + 1) * (k + 2) / 2 + (x == 0 ? k + 1 : x <= k + 1 ? x - 1 : x);
+    b = (int)((sqrt(8.0 * (double)id + 1.0) - 1.0) * 0.5);
+    while ((long)(b + 1) * (b + 2) / 2 <= id) ++b;
+    while ((long)b * (b + 1) / 2 > id) --b;
+    a = (int)(id - (long)b * (b + 1) / 2);
+  }
+  const bool upper = a <= k;  // a tile of W
+  load_block(linv, n, k * NB, k * NB, false, Zk, t);
+  if (a == k) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = t & 31, c = (t >> 5) + 8 * q;
+      Pa[r * CP + c] = r == c ? 1.0 : 0.0;
+    }
+  } else {
+    load_block(g, n, a * NB, k * NB, false, Pa, t);
+  }
+  if (!final_row) load_block(g, n, b * NB, k * NB, false, Pb, t);
+  // the tile itself: rows a, columns b (W) or rows b, columns a (G).  The product below
+  // has the tile's columns as its rows, so a lane's values are along 16 rows.
+  const int row0 = (upper ? a : b) * NB + 16 * (wave >> 1) + (lane & 15);
+  const int col0 = (upper ? b : a) * NB + 16 * (wave & 1) + (lane >> 4);
+  double c[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    c[q] = (final_row || a == k || row0 >= n || col0 + 4 * q >= n)
+               ? 0.0
+               : g[row0 + (long)(col0 + 4 * q) * n];
+  __syncthreads();
+  const f64x4 pa = block_nt(Pa, Zk, wave, lane);
+  f64x4 pb = pa;
+  if (!final_row && a != b) pb = block_nt(Pb, Zk, wave, lane);
+  const int pr = 16 * (wave & 1) + (lane >> 4), pc = 16 * (wave >> 1) + (lane & 15);
+  // row k of Z, off the diagonal: the transposes of P_a, a < k, from the tiles of b = k + 1
+  if (a < k && (final_row || b == k + 1)) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (k * NB + pc < n) linv[(k * NB + pc) + (long)(a * NB + pr + 4 * q) * n] = pa[q];
+  }
+  if (final_row) return;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    Pa[(pr + 4 * q) * CP + pc] = pa[q];
+    Pb[(pr + 4 * q) * CP + pc] = pb[q];
+  }
+  __syncthreads();
+  const f64x4 d = upper ? block_nt(Pb, Pa, wave, lane) : block_nt(Pa, Pb, wave, lane);
+  const bool next = a == k + 1 && b == k + 1;
+  if (next) __syncthreads();  // Pa becomes the block to be factored
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double v = c[q] - d[q];
+    if (next) {
+      const int r = row0 - b * NB, cc = col0 + 4 * q - b * NB;
+      Pa[r * CP + cc] = (row0 < n && col0 + 4 * q < n) ? v : (r == cc ? 1.0 : 0.0);
+    } else if (row0 < n && col0 + 4 * q < n) {
+      g[row0 + (long)(col0 + 4 * q) * n] = v;
+    }
+  }
+  if (!next) return;
+  __syncthreads();
+  if (t < 64) {
+    const int r = b * NB + (t & 31);
+    factor_block(Pa, Zk, r < n ? diag[r] : 1.0, t, err);
+  }
+  __syncthreads();
+  store_diag(linv, n, b, Zk, t);
 }
 
 template <typename TS, typename TD>
@@ -312,73 +442,21 @@ hipError_t gram(dk_ctx* c, const void* x, const void* y, long ld, int n_s, bool 
 
 // ------------------------------------------------------------ Cholesky --
 
-// Blocked right-looking Cholesky G = L L^T of the symmetric positive definite
-// g (n x n, column-major): the lower triangle of g is overwritten by L (the
-// strictly upper blocks are left as they were) and linv receives L^{-1}
-// (zero above the diagonal).  diag (n doubles) receives the diagonal of G; a
-// pivot below 1e-14 of it sets kErrNotSpd.
+// linv receives L^{-1} (zero above the diagonal) of the symmetric positive definite
+// g = L L^T (n x n, column-major); g is overwritten.  diag (n doubles) receives the
+// diagonal of G; a pivot below 1e-14 of it sets kErrNotSpd.
 hipError_t cholesky_inverse(dk_ctx* c, double* g, int n, double* linv, double* diag) {
-  hipError_t e;
-  hipLaunchKernelGGL(diag_kernel, dim3(grid_for(n)), dim3(256), 0, c->stream, g, n, diag);
-  hipLaunchKernelGGL(zero_kernel, dim3(grid_for((long)n * n)), dim3(256), 0, c->stream, linv,
-                     (long)n * n);
-  for (int k0 = 0; k0 < n; k0 += NB) {
-    const int nb = (n - k0 < NB) ? n - k0 : NB;
-    hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(256), 0, c->stream, g, n, k0, linv, diag,
-                       c->err_dev);
-    const int rest = n - k0 - nb;
-    if (rest <= 0) break;
-    double* a21 = g + (k0 + nb) + (long)k0 * n;
-    const double* li = linv + k0 + (long)k0 * n;
-    // panel: L21 = A21 L11^{-T}   (B(k,j) = Linv11(j,k): n-contiguous)
-    {
-      GemmArgs p;
-      p.M = rest; p.N = nb; p.K = nb;
-      p.A = a21; p.lda = n;
-      p.B = li; p.ldb = n;
-      p.C = a21; p.ldc = n;
-      e = launch_gemm<kF64, double, double, false, false, kStore, double, 32>(p, c->stream);
-      if (e != hipSuccess) return e;
-    }
-    // trailing update: A22 -= L21 L21^T (lower tiles)
-    {
-      double* a22 = g + (k0 + nb) + (long)(k0 + nb) * n;
-      GemmArgs u;
-      u.M = rest; u.N = rest; u.K = nb;
-      u.A = a21; u.lda = n;
-      u.B = a21; u.ldb = n;
-      u.C = a22; u.ldc = n;
-      u.Cin = a22; u.ldcin = n;
-      u.alpha = -1.0; u.beta = 1.0;
-      u.tile_sel = kLowerTiles;
-      e = launch_gemm<kF64, double, double, false, false, kStore, double, 32>(u, c->stream);
-      if (e != hipSuccess) return e;
-    }
+  const int nb = ceil_div(n, NB);
+  hipLaunchKernelGGL(chol_start_kernel, dim3(1 + grid_for((long)n * n)), dim3(256), 0, c->stream, g,
+                     n, linv, diag, c->err_dev);
+  for (int k = 0; k < nb; ++k) {
+    const long tiles = (long)nb * (nb + 1) / 2 - (long)(k + 1) * (k + 2) / 2;
+    const long wgs = k == nb - 1 ? k : tiles;
+    if (wgs > 0)
+      hipLaunchKernelGGL(chol_step_kernel, dim3((unsigned)wgs), dim3(256), 0, c->stream, g, n, k,
+                         linv, diag, c->err_dev);
   }
-  // off-diagonal blocks of L^{-1}, one block row at a time:
-  //   W = L[i0:i0+nb, 0:i0] Z[0:i0, 0:i0]        (into Z's block row i0)
-  //   Z[i0:i0+nb, 0:i0] = -Linv_ii W             (in place: a workgroup reads
-  //                                               its whole column tile of W
-  //                                               before writing it)
-  for (int i0 = NB; i0 < n; i0 += NB) {
-    const int nb = (n - i0 < NB) ? n - i0 : NB;
-    GemmArgs w;
-    w.M = nb; w.N = i0; w.K = i0;
-    w.A = g + i0; w.lda = n;        // L(i0+m, k), m-contiguous
-    w.B = linv; w.ldb = n;          // Z(k, j), k-contiguous
-    w.C = linv + i0; w.ldc = n;
-    e = launch_gemm<kF64, double, double, false, true, kStore, double, 32>(w, c->stream);
-    if (e != hipSuccess) return e;
-    GemmArgs t;
-    t.M = nb; t.N = i0; t.K = nb;
-    t.A = linv + i0 + (long)i0 * n; t.lda = n;   // Linv_ii, m-contiguous
-    t.B = linv + i0; t.ldb = n;                   // W(k, j) = linv[i0+k + j n]
-    t.C = linv + i0; t.ldc = n;
-    t.alpha = -1.0;
-    e = launch_gemm<kF64, double, double, false, true, kStore, double, 32>(t, c->stream);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  return hipGetLastError();
 }
 
 // ----------------------------------------------------- bf16 piece planes --

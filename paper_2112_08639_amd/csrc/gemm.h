@@ -42,6 +42,7 @@
 //   kPartial    P[s*M*N + m + n*M] = acc     (split-K partial sums of type TC; FP32
 //                                           partials lose nothing for FP32 accumulators)
 //   kAccumulate C[m + n*ldc] += alpha*acc
+//   kBiasSilu   C = acc + bias[m], act = SiLU(C);  kSiluGrad  C = acc SiLU'(zin)   (FP32)
 //   kRowSum     rowpart[nt*M + m] = sum_{n in tile} acc * R[m + n*ldr]
 #pragma once
 
@@ -59,7 +60,7 @@ constexpr bool split_bf16_mode(int m) {
 }
 // bf16 pieces per operand element in the split-at-store modes
 constexpr int split_pieces(int m) { return m == kBF16X6S ? 3 : 2; }
-enum GemmEpi { kStore = 0, kPartial = 1, kAccumulate = 2, kRowSum = 3 };
+enum GemmEpi { kStore = 0, kPartial = 1, kAccumulate = 2, kRowSum = 3, kBiasSilu = 4, kSiluGrad = 5 };
 enum TileSel { kAllTiles = 0, kUpperTiles = 1, kLowerTiles = 2 };
 
 struct GemmArgs {
@@ -97,6 +98,9 @@ struct GemmArgs {
   long a_plane = 0;           // the same for A (TA = __bf16; A(m,k) piece p = A[p*a_plane + m*lda + k])
   int a_lower_tri = 0;        // A(m,k) = 0 for k > m: stop the K loop at the tile's last m
   double* rowpart = nullptr;  // kRowSum output
+  const float* bias = nullptr;  // kBiasSilu: per row m
+  float* act = nullptr;         // kBiasSilu: SiLU of the result, laid out as C
+  const float* zin = nullptr;   // kSiluGrad: pre-activations, laid out as C
   const void* R = nullptr;    // kRowSum elementwise partner (column-major, ldr)
   long ldr = 0;
   // batched products (grid z = batch; no split-K): operand b of the batch is
@@ -126,6 +130,8 @@ __device__ __forceinline__ long xcd_work_item(long b, long total) {
   const long x = b % X, i = b / X;
   return (x < r) ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
 }
+
+__device__ __forceinline__ float sigmoid_f32(float z) { return 1.0f / (1.0f + expf(-z)); }
 
 template <int MODE> struct ModeTraits;
 template <> struct ModeTraits<kF64> { using CT = double; using Acc = f64x4; static constexpr int BK = 16; };
@@ -739,6 +745,40 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
         if (n >= g.N || m >= g.M) continue;
         float* cp = C + m + n * ldc;
         const float* sp = st + col * SP + row;
+        if constexpr (EPI == kBiasSilu || EPI == kSiluGrad) {
+          const long at = m + n * ldc;
+          const bool whole = vec_c && m + 4 <= g.M;
+          float v[4] = {sp[0], sp[1], sp[2], sp[3]}, o[4];
+          if constexpr (EPI == kSiluGrad) {
+            if (whole) {
+              const float4 z = *reinterpret_cast<const float4*>(g.zin + at);
+              o[0] = z.x; o[1] = z.y; o[2] = z.z; o[3] = z.w;
+            } else {
+              for (int e = 0; e < 4; ++e) o[e] = m + e < g.M ? g.zin[at + e] : 0.f;
+            }
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if constexpr (EPI == kBiasSilu) {
+              v[e] += g.bias[m + e < g.M ? m + e : g.M - 1];
+              o[e] = v[e] * sigmoid_f32(v[e]);
+            } else {
+              const float sg = sigmoid_f32(o[e]);
+              v[e] *= sg * (1.0f + o[e] * (1.0f - sg));
+            }
+          }
+          if (whole) {
+            *reinterpret_cast<float4*>(cp) = make_float4(v[0], v[1], v[2], v[3]);
+            if constexpr (EPI == kBiasSilu)
+              *reinterpret_cast<float4*>(g.act + at) = make_float4(o[0], o[1], o[2], o[3]);
+          } else {
+            for (int e = 0; e < 4 && m + e < g.M; ++e) {
+              cp[e] = v[e];
+              if constexpr (EPI == kBiasSilu) g.act[at + e] = o[e];
+            }
+          }
+          continue;
+        }
         if (vec_c && m + 4 <= g.M) {
           float4 cv = make_float4(0.f, 0.f, 0.f, 0.f);
           if constexpr (EPI == kAccumulate) cv = *reinterpret_cast<const float4*>(cp);
@@ -754,6 +794,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
       }
     }
   } else {
+    static_assert(EPI != kBiasSilu && EPI != kSiluGrad, "FP32 results through LDS only");
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
 #pragma unroll

@@ -645,9 +645,12 @@ __global__ __launch_bounds__(256, OCC) void scatter_kernel(ScatterArgs a) {
 
 // coef[(group n_s + col) 4 + proj % 4] = scale rowscale[proj] sum over the runs that hold
 // proj's group of the partial row (4 occ + proj % 4); zero past the last projector.  A
-// workgroup takes one projector and 64 columns; its
-// four waves sum interleaved quarters of the occurrences, two chains each.  occ null: the
-// dense runs, occurrence o of group g = o n_groups + g.
+// workgroup takes one projector and 64 columns; its four waves sum interleaved quarters
+// of the occurrences, kReduceDepth loads in flight each, which is what the time goes by
+// (two in flight: 12 us at 24^3 x 64 in FP64, 10 at 48^3 x 512 mixed; now 6 and 7; at 72^3 x
+// 2048 mixed, 108 groups, both 80, bound by the partials).  occ null: the dense runs,
+// occurrence o of group g = o n_groups + g.
+constexpr int kReduceDepth = 16;
 template <typename PT>
 __global__ __launch_bounds__(256) void sweep_reduce_kernel(const PT* __restrict__ part, int n_s,
                                                            int n_proj, int n_groups, int n_runs,
@@ -661,20 +664,21 @@ __global__ __launch_bounds__(256) void sweep_reduce_kernel(const PT* __restrict_
   const int proj = blockIdx.x, grp = proj >> 2, p = proj & 3;
   const int col = blockIdx.y * 64 + lane;
   const int o0 = occ ? occ_off[grp] : 0, o1 = occ ? occ_off[grp + 1] : n_runs;
-  auto at = [&](int o) -> double {
-    const long row = 4L * (occ ? occ[o] : (long)o * n_groups + grp) + p;
-    return (double)part[row * n_s + col];
-  };
-  double s0 = 0.0, s1 = 0.0;
+  double acc = 0.0;
   if (col < n_s) {
-    int o = o0 + wv;
-    for (; o + 4 < o1; o += 8) {
-      s0 += at(o);
-      s1 += at(o + 4);
+    for (int o = o0 + wv; o < o1; o += 4 * kReduceDepth) {
+      PT v[kReduceDepth];
+#pragma unroll
+      for (int i = 0; i < kReduceDepth; ++i) {
+        const int oi = min(o + 4 * i, o1 - 1);
+        v[i] = part[(4L * (occ ? occ[oi] : (long)oi * n_groups + grp) + p) * n_s + col];
+      }
+#pragma unroll
+      for (int i = 0; i < kReduceDepth; ++i)
+        if (o + 4 * i < o1) acc += (double)v[i];
     }
-    for (; o < o1; o += 4) s0 += at(o);
   }
-  sh[wv][lane] = s0 + s1;
+  sh[wv][lane] = acc;
   __syncthreads();
   if (wv == 0 && col < n_s) {
     const double s = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);

@@ -49,6 +49,10 @@ struct NtArgs {
   long bs_a = 0, bs_b = 0, bs_c = 0, bs_cin = 0;
   int upper = 0;             // square: the tiles of the upper triangle only
   int mirror = 0;            // with upper, store: each off-diagonal tile's transpose too
+  // with mirror: per tile of every operand of the batch, the tile's share (and its
+  // mirror image's) of tr C and <S, C>_F of the symmetric result, S bs_c apart
+  const double* S = nullptr;
+  double* part = nullptr;
 };
 
 // Slab loader of one operand: BT rows by BK, along k.
@@ -178,6 +182,7 @@ __global__ __launch_bounds__(256, OCC) void nt_f64_kernel(NtArgs a) {
             acc[j][i] = mfma_f64(fb[j][r >> 1][r & 1], fa[i][r >> 1][r & 1], acc[j][i]);
     }
   }
+  double trace = 0.0, dot = 0.0;  // of this lane's elements, the mirrored ones included
   // lane: m = c16 of block i, n = g + 4 q of block j
 #pragma unroll
   for (int j = 0; j < MI; ++j)
@@ -196,8 +201,29 @@ __global__ __launch_bounds__(256, OCC) void nt_f64_kernel(NtArgs a) {
           double* const C = a.C + bi * a.bs_c;
           C[m + (long)n * a.ldc] = out;
           if (a.mirror && mt != nt) C[n + (long)m * a.ldc] = out;
+          if (a.S) {
+            const double v2 = (a.S + bi * a.bs_c)[m + (long)n * a.ldc] * out;
+            dot += mt != nt ? 2.0 * v2 : v2;
+            if (m == n) trace += out;
+          }
         }
       }
+  if constexpr (!PARTIAL) {
+    if (!a.S) return;
+    for (int o = 32; o > 0; o >>= 1) {
+      trace += __shfl_xor(trace, o);
+      dot += __shfl_xor(dot, o);
+    }
+    __syncthreads();  // the slabs are done with
+    if (lane == 0) {
+      nt_lds[2 * wave] = trace;
+      nt_lds[2 * wave + 1] = dot;
+    }
+    __syncthreads();
+    if (tid < 2)
+      a.part[2 * (bi * tiles + tile) + tid] =
+          (nt_lds[tid] + nt_lds[2 + tid]) + (nt_lds[4 + tid] + nt_lds[6 + tid]);
+  }
 }
 
 constexpr size_t nt_lds_bytes(int BT, int BK) { return (size_t)4 * BT * (BK + 2) * sizeof(double); }
@@ -226,11 +252,16 @@ inline hipError_t launch_nt(const NtArgs& a, hipStream_t st) {
 // tiles) 32 against 44; from 32 on (1152 tiles) 64 x 64 run at the matrix rate (94 us,
 // 46 TFLOP/s counted over the upper triangle).  Against the general template: two squarings at
 // n = 512 20.6 -> 15.8 us, at n = 2048 0.60 -> 0.36 ms.
+constexpr int kSymmetricTile = 32;  // the smaller of the two
+inline int symmetric_tile(int n, int batch) {
+  const long t = ceil_div(n, 64);
+  return t * (t + 1) / 2 * batch < 512 ? kSymmetricTile : 64;
+}
 inline hipError_t symmetric_product(NtArgs g, hipStream_t st) {
   g.upper = 1;
   g.mirror = 1;
-  const long t = ceil_div(g.M, 64), tiles = t * (t + 1) / 2 * g.batch;
-  if (tiles < 512) return launch_nt<double, double, false, 32, 32, 4>(g, st);
+  if (symmetric_tile(g.M, g.batch) == kSymmetricTile)
+    return launch_nt<double, double, false, 32, 32, 4>(g, st);
   return launch_nt<double, double, false, 64, 16, 4>(g, st);
 }
 

@@ -617,21 +617,17 @@ __global__ __launch_bounds__(256) void gersh_reduce_kernel(const double* lower, 
 
 // blockIdx.y = mode; mode 0: M = sym(H) - s I, s = scal[0];  mode 1:
 // M = s I - sym(H), s = scal[3].  X = M / tr M.  Mode m writes M + m n^2, X + m n^2,
-// and sets its sequence's product scale alpha[m] = 1 and reduction counter cnt[m] = 0.
+// and sets its sequence's product scale alpha[m] = 1.
 __global__ __launch_bounds__(256) void squaring_init_kernel(const double* __restrict__ h, int n,
                                                             const double* __restrict__ scal,
                                                             double* __restrict__ M,
                                                             double* __restrict__ X,
-                                                            double* __restrict__ alpha,
-                                                            unsigned* __restrict__ cnt) {
+                                                            double* __restrict__ alpha) {
   const long nn = (long)n * n;
   const int mode = blockIdx.y;
   M += mode * nn;
   X += mode * nn;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    alpha[mode] = 1.0;
-    cnt[mode] = 0u;
-  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) alpha[mode] = 1.0;
   const double sft = mode == 0 ? scal[0] : scal[3];
   const double trm = mode == 0 ? scal[2] - n * sft : n * sft - scal[2];
   for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < nn;
@@ -645,73 +641,46 @@ __global__ __launch_bounds__(256) void squaring_init_kernel(const double* __rest
   }
 }
 
-// Statistics of squaring step `step` of sequence y = m0 + blockIdx.y (the pair
-// M + y n^2, Y + y n^2): per-block partial sums of tr Y and <M, Y>_F into
-// part + 2 y gridDim.x; the last block of the sequence to finish (an atomic
-// count, no waiting) sums the partials in block order and writes
-// est[y * est_stride + step] = <M, Y> / tr Y and alpha[y] = 1 / (tr Y)^2, the
-// scale of the next product Y' = alpha Y Y (= (Y / tr Y)^2), and rearms the count.
-__global__ __launch_bounds__(256) void squaring_stats_kernel(const double* __restrict__ M,
-                                                             const double* __restrict__ Y, int n,
-                                                             double* __restrict__ part, int m0,
-                                                             double* __restrict__ est,
-                                                             int est_stride, int step,
-                                                             double* __restrict__ alpha,
-                                                             unsigned* __restrict__ cnt) {
+// The end of a squaring, one workgroup per sequence: tr Y and <M, Y>_F from the `tiles`
+// partials that its product left, the estimate <M, Y> / tr Y to pinned host memory, and
+// 1 / (tr Y)^2, the scale of the next product Y' = alpha Y Y (= (Y / tr Y)^2).  (A kernel
+// reading M and Y for the two sums took 10 us at n = 512 and 72 us at n = 2048, and the
+// copy of the estimates with the gaps around it 13 us; this one and its gap 5.)
+__global__ __launch_bounds__(256) void squaring_finish_kernel(const double* __restrict__ part,
+                                                              long tiles, double* host_est,
+                                                              int est_stride,
+                                                              double* __restrict__ alpha) {
   __shared__ double sh[4];
-  __shared__ bool last;
-  const long nn = (long)n * n;
-  const long y = m0 + (long)blockIdx.y;
-  M += y * nn;
-  Y += y * nn;
-  part += 2L * y * gridDim.x;
-  double my = 0.0, ty = 0.0;
-  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < nn;
-       e += (long)gridDim.x * blockDim.x) {
-    const double v = Y[e];
-    my += M[e] * v;
-    if (e % (n + 1) == 0) ty += v;
-  }
-  my = block_sum256(my, sh);
-  ty = block_sum256(ty, sh);
-  if (threadIdx.x == 0) {
-    part[2 * blockIdx.x] = ty;
-    part[2 * blockIdx.x + 1] = my;
-    __threadfence();  // the partials are visible before the count moves
-    last = atomicAdd(cnt + y, 1u) == gridDim.x - 1;
-  }
-  __syncthreads();
-  if (!last || threadIdx.x >= 64) return;
-  __threadfence();  // every other block's partials are visible
+  part += 2 * tiles * blockIdx.x;
   double t = 0.0, m = 0.0;
-  for (int i = threadIdx.x; i < (int)gridDim.x; i += 64) {
+  for (long i = threadIdx.x; i < tiles; i += 256) {
     t += part[2 * i];
     m += part[2 * i + 1];
   }
-  for (int o = 32; o > 0; o >>= 1) {
-    t += __shfl_xor(t, o);
-    m += __shfl_xor(m, o);
-  }
+  t = block_sum256(t, sh);
+  m = block_sum256(m, sh);
   if (threadIdx.x == 0) {
-    est[y * est_stride + step] = m / t;
-    alpha[y] = 1.0 / (t * t);
-    cnt[y] = 0u;
+    host_est[blockIdx.x * est_stride] = m / t;
+    alpha[blockIdx.x] = 1.0 / (t * t);
   }
 }
 
 __global__ void set_scalar_kernel(double* p, double v) { p[0] = v; }
 
 constexpr int SB_MAX_STEPS = 48;
-constexpr int SB_PARTS = 128;
+// partial sums of a squaring: two per tile of two sequences
+size_t sb_parts(int n) {
+  const size_t t = ceil_div(n, kSymmetricTile);
+  return 4 * (t * (t + 1) / 2);
+}
 
 }  // namespace
 
 size_t spectral_ws_bytes(int n) {
   const size_t nn = (size_t)n * n;
   return 3 * ws_slice(2 * nn * sizeof(double)) + 3 * ws_slice((size_t)n * sizeof(double)) +
-         ws_slice(8 * sizeof(double)) + ws_slice(4 * SB_PARTS * sizeof(double)) +
-         ws_slice(2 * SB_MAX_STEPS * sizeof(double)) + ws_slice(2 * sizeof(double)) +
-         ws_slice(2 * sizeof(unsigned));
+         ws_slice(8 * sizeof(double)) + ws_slice(sb_parts(n) * sizeof(double)) +
+         ws_slice(2 * sizeof(double));
 }
 
 // Both squaring sequences side by side (M, X, Y hold the two n x n
@@ -722,13 +691,12 @@ size_t spectral_ws_bytes(int n) {
 // (alpha, set by the statistics of the step before), so no pass rescales the
 // matrices.
 static hipError_t squaring_pair(dk_ctx* c, const double* hs, int n, double* M, double* X,
-                                double* Y, double* scal, double* part, double* est, double* alpha,
-                                unsigned* cnt, double* q, int* steps) {
+                                double* Y, double* scal, double* part, double* alpha, double* q,
+                                int* steps) {
   const long nn = (long)n * n;
-  const int blocks = (int)((nn + 255) / 256 < SB_PARTS ? (nn + 255) / 256 : SB_PARTS);
   const int eblocks = (int)((nn + 255) / 256 < 4096 ? (nn + 255) / 256 : 4096);
   hipLaunchKernelGGL(squaring_init_kernel, dim3(eblocks, 2), dim3(256), 0, c->stream, hs, n, scal,
-                     M, X, alpha, cnt);
+                     M, X, alpha);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   double cur[2] = {0, 0};
@@ -736,16 +704,17 @@ static hipError_t squaring_pair(dk_ctx* c, const double* hs, int n, double* M, d
   bool conv = false;
   int k = 0, squarings = 0;
   // For N_s <= 1024 the host checks step k - 1 while step k runs: each step's
-  // estimates are copied to one of two pinned buffers and an event marks the
-  // copy done, so the GPU does not idle during the check (a converged sequence
+  // estimates go to their places in pinned memory and an event marks the step
+  // done, so the GPU does not idle during the check (a converged sequence
   // may run one squaring more, which is discarded): al32 0.86 -> 0.72 ms.
   // Larger matrices check each step as it ends (a squaring outweighs the wait).
-  // (Two steps behind, with three buffers, was slower: 0.72 -> 0.77 ms.)
+  // (Two steps behind was slower: 0.72 -> 0.77 ms.)
   const int lag = n <= 1024 ? 1 : 0;
   constexpr int kBufs = 2;
-  constexpr size_t kEstBytes = 2 * SB_MAX_STEPS * sizeof(double);
   if (!c->sb_host) {
-    if ((e = hipHostMalloc((void**)&c->sb_host, kBufs * kEstBytes)) != hipSuccess) return e;
+    if ((e = hipHostMalloc((void**)&c->sb_host, 2 * SB_MAX_STEPS * sizeof(double))) !=
+        hipSuccess)
+      return e;
     for (hipEvent_t& ev : c->sb_ev)
       if ((e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) return e;
   }
@@ -764,20 +733,22 @@ static hipError_t squaring_pair(dk_ctx* c, const double* hs, int n, double* M, d
     g.batch = active;
     squarings += active;
     g.bs_a = g.bs_b = g.bs_c = nn;
-    // X_k is symmetric (a power of M): upper tiles only, mirrored
+    // X_k is symmetric (a power of M): upper tiles only, mirrored; the product also leaves
+    // the estimate and the scale of the next one
+    g.S = M + first * nn;
+    g.part = part;
     e = symmetric_product(g, c->stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(squaring_stats_kernel, dim3(blocks, active), dim3(256), 0, c->stream, M,
-                       Q, n, part, first, est, SB_MAX_STEPS, k, alpha, cnt);
+    const long t = ceil_div(n, symmetric_tile(n, active));
+    hipLaunchKernelGGL(squaring_finish_kernel, dim3(active), dim3(256), 0, c->stream, part,
+                       t * (t + 1) / 2, c->sb_host + first * SB_MAX_STEPS + k, SB_MAX_STEPS,
+                       alpha + first);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    double* hb = c->sb_host + (k % kBufs) * 2 * SB_MAX_STEPS;
-    if ((e = hipMemcpyAsync(hb, est, kEstBytes, hipMemcpyDeviceToHost, c->stream)) != hipSuccess)
-      return e;
     if ((e = hipEventRecord(c->sb_ev[k % kBufs], c->stream)) != hipSuccess) return e;
     const int j = k - lag;  // the step checked now
     if (j >= 5) {
       if ((e = hipEventSynchronize(c->sb_ev[j % kBufs])) != hipSuccess) return e;
-      const double* two = c->sb_host + (j % kBufs) * 2 * SB_MAX_STEPS;
+      const double* two = c->sb_host;
       bool finite = true;
       for (int m = 0; m < 2; ++m) {
         if (done_m[m]) continue;
@@ -818,10 +789,8 @@ hipError_t spectral_bounds(dk_ctx* c, const double* hs, int n, void* ws, double*
   double* upper = cur.take<double>(n);
   double* diag = cur.take<double>(n);
   double* scal = cur.take<double>(8);
-  double* part = cur.take<double>(4 * SB_PARTS);
-  double* est = cur.take<double>(2 * SB_MAX_STEPS);
+  double* part = cur.take<double>(sb_parts(n));
   double* alpha = cur.take<double>(2);
-  unsigned* cnt = cur.take<unsigned>(2);
   if (!cur.ok) return hipErrorInvalidValue;
   hipLaunchKernelGGL(gersh_rows_kernel, dim3((n + 3) / 4), dim3(256), 0, c->stream, hs, n, lower,
                      upper, diag);
@@ -849,7 +818,7 @@ hipError_t spectral_bounds(dk_ctx* c, const double* hs, int n, void* ws, double*
   hipLaunchKernelGGL(set_scalar_kernel, dim3(1), dim3(1), 0, c->stream, scal + 3, sh);
   double q[2] = {0, 0};
   int k = 0;
-  if ((e = squaring_pair(c, hs, n, M, X, Y, scal, part, est, alpha, cnt, q, &k)) != hipSuccess)
+  if ((e = squaring_pair(c, hs, n, M, X, Y, scal, part, alpha, q, &k)) != hipSuccess)
     return e;
   *hi = q[0] + gl[0];
   *lo = sh - q[1];

@@ -124,7 +124,10 @@ __global__ __launch_bounds__(256) void dense_rows_kernel(const int* __restrict__
 // for its tile of the next block as well (373248 x 2048, 432 projectors, two pieces: 1.60
 // against 1.16 ms).  Measured: 66 us at 110592 x 512 over 128 projectors (3.4 TB/s), before 80
 // over the dense table; 1.10 against 1.72 ms at 373248 x 2048; FP64 274 against 342 us
-// at 110592 x 512, bound by MFMA on row blocks of which half the slots are live.
+// at 110592 x 512, bound by MFMA on row blocks of which half the slots are live.  In the
+// mixed kernel the feeding waves run at the highest priority (64.6 -> 62.8 us and, over
+// 432 projectors, 1.23 -> 1.17 ms); in FP64, where they share SIMDs whose matrix pipes are
+// full, at the same as the others (higher: 272 -> 297 us).
 
 constexpr int kFeedWaves = 4;
 constexpr int kFeedDepth = 2;
@@ -200,6 +203,7 @@ void integrals_mixed_kernel(SweepArgs a) {
   const long w = xcd_work_item(blockIdx.x, (long)gridDim.x);
   const SweepRun run(a, (int)(w / a.ntiles));
   if (wave >= CW) {
+    __builtin_amdgcn_s_setprio(3);  // few instructions, and the others wait for them
     SweepFeed<piece_units(NP), 96> feed{(const f32x4*)a.tab, StageCursor(run),
                                         (int)threadIdx.x - 64 * CW};
     feed.run(ring);
@@ -473,6 +477,14 @@ void integrals_f64_kernel(SweepArgs a) {
 // next tile replace this one's as they are used, and nothing passes through LDS.  The
 // four waves of a workgroup take consecutive points of the same columns.  The grid is two
 // waves per SIMD, every workgroup with an equal share of the tiles, points outermost.
+// (Shares by the cost of their blocks instead of equal ones change nothing.)
+//
+// MFMA alone takes half of the time and memory alone two thirds (72^3 x 2048, 432
+// projectors: 1.1 and 1.24 of 2.0 ms), and what the two waves of a SIMD overlap depends on
+// their priorities: highest while a wave multiplies, lowest while it issues the next
+// tile's loads: 122 -> 112 us at 110592 x 512 over 128 projectors, 2.02 -> 1.94 ms at
+// 373248 x 2048, FP64 214 -> 206 us at 110592 x 512.  (The reverse order: 145 us, 2.96
+// ms.)
 
 // The columns are the rows of the MFMA and the points its columns, the lane's points of
 // the row blocks being consecutive: the 16 lanes of a column then move 256 consecutive
@@ -568,7 +580,9 @@ __device__ __forceinline__ void scatter_tiles(const ScatterArgs& a, int b, int m
   load_tile(ya, t0);
   auto tile = [&](int t, Vec (&y)[4], Vec (&yn)[4]) {
     const int tn = min(t + 1, t1 - 1);
+    __builtin_amdgcn_s_setprio(0);
     load_tile(yn, tn);
+    __builtin_amdgcn_s_setprio(3);
     const long next = min(16 * tn + c16, a.n_s - 1);
     Acc s[MB];
 #pragma unroll
@@ -581,6 +595,7 @@ __device__ __forceinline__ void scatter_tiles(const ScatterArgs& a, int b, int m
         for (int mb = 0; mb < MB; ++mb) s[mb] = mfma_t(cv[q][j], av[q][j][mb], s[mb]);
       load4(cv[q], cp[q] + next * 4);
     }
+    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       T* p = y_at(t, r);

@@ -39,6 +39,9 @@ struct dk_ctx {
   int* klist = nullptr;
   int* kcount = nullptr;
   int* geoff = nullptr;
+  int* gperm = nullptr;  // group at each place of the sorted order, and its inverse
+  unsigned long long* gcentre = nullptr;
+  double* ggamma = nullptr;  // gamma in that order, four per group
   int n_groups = 0;
   long g_entries = 0;   // (block, live group) pairs
   long g_capacity = 0;  // entries the tables have room for

@@ -11,25 +11,21 @@
 //   kF64    FP64 MFMA 16x16x4, operands converted to double (FP32 operands are
 //           widened exactly).
 //   kF32    FP32 MFMA 16x16x4.
-//   kBF16X3 split-BF16: every FP32 operand x = hi + lo (bf16 each) and
-//           A B ~ A_hi B_hi + A_hi B_lo + A_lo B_hi, FP32 accumulation
-//           (MFMA 16x16x32 bf16).  Relative error per product ~ 2^-16.
 //   kBF16   plain BF16: FP32 operands rounded to bf16, one MFMA 16x16x32,
 //           FP32 accumulation (~2^-8 per product).
-//   kBF16X6 three-piece split x = hi + mid + lo (bf16 each); the six products
+//   kBF16X3S split-BF16: every FP32 operand x = hi + lo (bf16 each) and
+//           A B ~ A_hi B_hi + A_hi B_lo + A_lo B_hi, FP32 accumulation
+//           (MFMA 16x16x32 bf16).  Relative error per product ~ 2^-16.
+//   kBF16X6S three-piece split x = hi + mid + lo (bf16 each); the six products
 //           whose exponent sum is at most 2^-16 (lo.hi, mid.mid, hi.lo,
 //           mid.hi, hi.mid, hi.hi, smallest first) leave ~2^-24 per product,
 //           the FP32 level.
-//   kBF16X3S, kBF16X6S  the same products with every operand element split
-//           once, on its way into LDS: LDS holds the bf16 pieces (one plane
-//           per piece, rows of BK + 8 values), a single slab buffer, and the
-//           waves read whole 8-value fragments of each piece.  In kBF16X3 /
-//           kBF16X6 LDS holds FP32 and each wave splits the fragments it
-//           reads, so an element is split once per wave row or column that
-//           uses it and the VALU work rivals the MFMA work.  Operands that are
-//           contiguous along m (n) move as 4 x 4 blocks (four k rows of four
-//           consecutive m), so that the pieces of four consecutive k are
-//           written as one 8-byte LDS store.  Block masks apply; k-lists do not.
+//           In both every operand element is split once, on its way into LDS:
+//           LDS holds the bf16 pieces (one plane per piece, rows of BK + 8
+//           values), a single slab buffer, and the waves read whole 8-value
+//           fragments of each piece.  Operands that are contiguous along m (n)
+//           move as 4 x 4 blocks (four k rows of four consecutive m), so that
+//           the pieces of four consecutive k are written as one 8-byte LDS store.
 //
 // Operand layouts (column-major storage, lda/ldb leading dimensions)
 //   A k-contiguous: A(m,k) = A[m*lda + k]     (A^T of a column-major K x M array)
@@ -41,7 +37,6 @@
 //   kStore      C[m + n*ldc] = alpha*acc + beta*Cin[m + n*ldcin]   (Cin may alias C)
 //   kPartial    P[s*M*N + m + n*M] = acc     (split-K partial sums of type TC; FP32
 //                                           partials lose nothing for FP32 accumulators)
-//   kAccumulate C[m + n*ldc] += alpha*acc
 //   kBiasSilu   C = acc + bias[m], act = SiLU(C);  kSiluGrad  C = acc SiLU'(zin)   (FP32)
 //   kRowSum     rowpart[nt*M + m] = sum_{n in tile} acc * R[m + n*ldr]
 #pragma once
@@ -52,16 +47,15 @@
 
 namespace dk {
 
-enum GemmMode { kF64 = 0, kF32 = 1, kBF16X3 = 2, kBF16X6 = 3, kBF16 = 4, kBF16X3S = 5,
-                kBF16X6S = 6 };
+enum GemmMode { kF64 = 0, kF32 = 1, kBF16 = 2, kBF16X3S = 3, kBF16X6S = 4 };
 constexpr bool split_store_mode(int m) { return m == kBF16X3S || m == kBF16X6S; }
 constexpr bool split_bf16_mode(int m) {
-  return m == kBF16X3 || m == kBF16X6 || m == kBF16 || split_store_mode(m);
+  return m == kBF16 || split_store_mode(m);
 }
 // bf16 pieces per operand element in the split-at-store modes
 constexpr int split_pieces(int m) { return m == kBF16X6S ? 3 : 2; }
-enum GemmEpi { kStore = 0, kPartial = 1, kAccumulate = 2, kRowSum = 3, kBiasSilu = 4, kSiluGrad = 5 };
-enum TileSel { kAllTiles = 0, kUpperTiles = 1, kLowerTiles = 2 };
+enum GemmEpi { kStore = 0, kPartial = 1, kRowSum = 2, kBiasSilu = 3, kSiluGrad = 4 };
+enum TileSel { kAllTiles = 0, kUpperTiles = 1 };
 
 struct GemmArgs {
   int M = 0, N = 0, K = 0;
@@ -69,7 +63,7 @@ struct GemmArgs {
   long lda = 0;
   const void* B = nullptr;
   long ldb = 0;
-  void* C = nullptr;          // output (kStore / kAccumulate) or partial buffer (kPartial)
+  void* C = nullptr;          // output (kStore) or partial buffer (kPartial)
   long ldc = 0;
   const void* Cin = nullptr;  // kStore: source of the beta term
   long ldcin = 0;
@@ -77,47 +71,21 @@ struct GemmArgs {
   int splits = 1;             // split-K count (grid z)
   int k_per_split = 0;        // multiple of 64
   int tile_sel = kAllTiles;
-  // block-sparse A: rows [r*kmask_mrows, (r+1)*kmask_mrows) of k-block kb are
-  // all zero if kmask[r*kmask_stride + kb] == 0; a tile skips a K slab when
-  // every mask row it overlaps is zero there
-  const uint8_t* kmask = nullptr;
-  long kmask_stride = 0;
-  int kmask_blk = 64;         // K elements per mask entry (multiple of the K slab)
-  int kmask_mrows = 64;       // M rows per mask row
-  // indirect K (no split-K, no mask): m-tile mt runs over the K positions
-  // 0 .. 4 klist_count[mt] - 1, position p standing for
-  // k = 4 klist[mt * klist_stride + p / 4] + p % 4 (groups of 4 consecutive k;
-  // a k >= K reads zero).  The K slab must be a multiple of 4.
-  const int* klist = nullptr;
-  const int* klist_count = nullptr;
-  long klist_stride = 0;
   int b_upper_tri = 0;        // B(k,n) = 0 for k > n: stop the K loop at the tile's last n
   // split-at-store modes with TB = __bf16: B comes pre-split, its NP piece planes
   // b_plane elements apart, each k-contiguous (B(k,n) piece p = B[p*b_plane + n*ldb + k])
   long b_plane = 0;
-  long a_plane = 0;           // the same for A (TA = __bf16; A(m,k) piece p = A[p*a_plane + m*lda + k])
-  int a_lower_tri = 0;        // A(m,k) = 0 for k > m: stop the K loop at the tile's last m
   double* rowpart = nullptr;  // kRowSum output
   const float* bias = nullptr;  // kBiasSilu: per row m
   float* act = nullptr;         // kBiasSilu: SiLU of the result, laid out as C
   const float* zin = nullptr;   // kSiluGrad: pre-activations, laid out as C
   const void* R = nullptr;    // kRowSum elementwise partner (column-major, ldr)
   long ldr = 0;
-  // batched products (grid z = batch; no split-K): operand b of the batch is
-  // offset by b * stride elements (strides may be negative)
-  int batch = 1;
-  long bs_a = 0, bs_b = 0, bs_c = 0, bs_cin = 0;
   // tile order: 0 = m fastest (neighbours share B and the K-slab), 1 = n
   // fastest (neighbours share the A rows); xcd_groups = 1 hands each XCD a
   // contiguous range of that order, 0 keeps the hardware's round-robin
   int n_fastest = 0;
   int xcd_groups = 1;
-  // symmetric results (kStore, FP64 epilogue, tile_sel = kUpperTiles, square
-  // tiles): each off-diagonal tile also stores its transpose, so that only the
-  // upper tiles are computed and C comes out whole and exactly symmetric
-  int mirror = 0;
-  // kStore: alpha is multiplied by alpha_dev[b] (device memory) for operand b of the batch
-  const double* alpha_dev = nullptr;
 };
 
 // Work-item index of this workgroup.  Workgroups are dispatched round-robin
@@ -136,13 +104,11 @@ __device__ __forceinline__ float sigmoid_f32(float z) { return 1.0f / (1.0f + ex
 template <int MODE> struct ModeTraits;
 template <> struct ModeTraits<kF64> { using CT = double; using Acc = f64x4; static constexpr int BK = 16; };
 template <> struct ModeTraits<kF32> { using CT = float; using Acc = f32x4; static constexpr int BK = 16; };
-template <> struct ModeTraits<kBF16X3> { using CT = float; using Acc = f32x4; static constexpr int BK = 32; };
-template <> struct ModeTraits<kBF16X6> { using CT = float; using Acc = f32x4; static constexpr int BK = 32; };
 template <> struct ModeTraits<kBF16> { using CT = float; using Acc = f32x4; static constexpr int BK = 32; };
 template <> struct ModeTraits<kBF16X3S> { using CT = float; using Acc = f32x4; static constexpr int BK = 32; };
 template <> struct ModeTraits<kBF16X6S> { using CT = float; using Acc = f32x4; static constexpr int BK = 32; };
 
-// Split-at-store slab movement (kBF16X3S / kBF16X6S).  An operand slab holds R
+// Split-at-store slab movement.  An operand slab holds R
 // rows (m or n) by BK k.  k-contiguous operands: groups of 4 consecutive k of one
 // row, R*BK/1024 per thread.  Row-contiguous operands: one 4 x 4 block per
 // thread (k 4*(t % (BK/4)) .., rows 4*(t / (BK/4)) ..) while t < R*BK/16, so that
@@ -307,7 +273,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
   constexpr int MI = BM / 32;          // 16x16 MFMA blocks per wave along m
   constexpr int NJ = BN / 32;          // ... along n
   static_assert(!split_bf16_mode(MODE) || BK % 32 == 0, "bf16 slab must hold whole 16x16x32 steps");
-  // F64/F32: slab stored [k][m] (pitch BM+1); BF16X3: [m][k] (pitch BK+4), so a
+  // F64/F32: slab stored [k][m] (pitch BM+1); BF16: [m][k] (pitch BK+4), so a
   // lane's 8 consecutive k are contiguous for the 16x16x32 operand.
   constexpr bool KMAJOR = split_bf16_mode(MODE);
   constexpr int PA = KMAJOR ? (BK + 4) : (BM + 1);
@@ -332,40 +298,26 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
   CT* sB = smem_ab + 2 * SLAB_A;
   __shared__ double red[2][BM];
 
-  // decode (m tile, n tile, split or batch) from the XCD-grouped item index
+  // decode (m tile, n tile, split) from the XCD-grouped item index
   const long gx = gridDim.x, gy = gridDim.y;
   const long total = gx * gy * (long)gridDim.z;
   const long lin = blockIdx.x + gx * (blockIdx.y + gy * (long)blockIdx.z);
   const long w = g.xcd_groups ? xcd_work_item(lin, total) : lin;
   int mt, nt;
-  long zi;
-  if (g.n_fastest) { nt = (int)(w % gy); mt = (int)((w / gy) % gx); zi = w / (gx * gy); }
-  else { mt = (int)(w % gx); nt = (int)((w / gx) % gy); zi = w / (gx * gy); }
-  const int s = (g.batch > 1) ? 0 : (int)zi;
-  const long bidx = (g.batch > 1) ? zi : 0;
+  if (g.n_fastest) { nt = (int)(w % gy); mt = (int)((w / gy) % gx); }
+  else { mt = (int)(w % gx); nt = (int)((w / gx) % gy); }
+  const int s = (int)(w / (gx * gy));
   if (g.tile_sel == kUpperTiles && mt > nt) return;
-  if (g.tile_sel == kLowerTiles && mt < nt) return;
   const int m0 = mt * BM, n0 = nt * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = (wave & 1) * (BM / 2), wn = (wave >> 1) * (BN / 2);
 
-  long k_begin = (long)s * g.k_per_split;
+  const long k_begin = (long)s * g.k_per_split;
   long k_end = k_begin + g.k_per_split;
   if (k_end > g.K) k_end = g.K;
   if (g.b_upper_tri) { long lim = (long)n0 + BN; if (k_end > lim) k_end = lim; }
-  if (g.a_lower_tri) { long lim = (long)m0 + BM; if (k_end > lim) k_end = lim; }
-  static_assert(BK % 4 == 0, "k-list groups of 4 must not straddle a slab");
-  const int* __restrict__ krow = nullptr;
-  if (g.klist) {
-    krow = g.klist + (long)mt * g.klist_stride;
-    k_begin = 0;
-    k_end = 4L * g.klist_count[mt];
-  }
-  // K position -> k (identity without a k-list)
-  auto kmap = [&](long p) -> long { return krow ? 4L * krow[p >> 2] + (p & 3) : p; };
-
-  const TA* __restrict__ A = (const TA*)g.A + bidx * g.bs_a;
-  const TB* __restrict__ B = (const TB*)g.B + bidx * g.bs_b;
+  const TA* __restrict__ A = (const TA*)g.A;
+  const TB* __restrict__ B = (const TB*)g.B;
 
   Acc acc[NJ][MI];
 #pragma unroll
@@ -373,20 +325,6 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
 #pragma unroll
     for (int i = 0; i < MI; ++i) acc[j][i] = Acc{0, 0, 0, 0};
 
-  // first slab at or after k that the block mask does not skip
-  const int mrow0 = g.kmask ? m0 / g.kmask_mrows : 0;
-  const int mrow1 = g.kmask ? (((m0 + BM < g.M) ? m0 + BM : g.M) - 1) / g.kmask_mrows : 0;
-  auto live = [&](long k) {
-    const long kb = k / g.kmask_blk;
-    for (int r = mrow0; r <= mrow1; ++r)
-      if (g.kmask[(long)r * g.kmask_stride + kb]) return true;
-    return false;
-  };
-  auto next_live = [&](long k) {
-    if (g.kmask)
-      while (k < k_end && !live(k)) k += BK;
-    return k;
-  };
   // Operand slabs move in groups of VA (VB) elements consecutive along the
   // operand's contiguous dimension: one vector load per group when the whole
   // group is in range and aligned, element loads otherwise.
@@ -405,11 +343,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
       const int c = (grp % CA) * VA, o = grp / CA;
       const int m = AKC ? o : c, k = AKC ? c : o;
       const long gm = m0 + m, gk = k0 + k;
-      // position gk holds k = ka; a group of VA <= 4 positions stays inside one k-list group
-      const long ka = (gk < k_end) ? kmap(gk) : gk;
-      const bool full = AKC ? (gm < g.M && gk + VA <= k_end && ka + VA <= g.K)
-                            : (gk < k_end && ka < g.K && gm + VA <= g.M);
-      const TA* src = AKC ? A + gm * g.lda + ka : A + ka * g.lda + gm;
+      const bool full = AKC ? (gm < g.M && gk + VA <= k_end) : (gk < k_end && gm + VA <= g.M);
+      const TA* src = AKC ? A + gm * g.lda + gk : A + gk * g.lda + gm;
       if (vec_a && full) {
         typedef TA vt __attribute__((ext_vector_type(VA)));
         const vt v = *reinterpret_cast<const vt*>(src);
@@ -418,8 +353,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
       } else {
 #pragma unroll
         for (int j = 0; j < VA; ++j) {
-          const bool in = AKC ? (gm < g.M && gk + j < k_end && ka + j < g.K)
-                              : (gk < k_end && ka < g.K && gm + j < g.M);
+          const bool in = AKC ? (gm < g.M && gk + j < k_end) : (gk < k_end && gm + j < g.M);
           ra[r * VA + j] = in ? (CT)src[j] : (CT)0;
         }
       }
@@ -430,10 +364,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
       const int c = (grp % CB) * VB, o = grp / CB;
       const int n = BKC ? o : c, k = BKC ? c : o;
       const long gn = n0 + n, gk = k0 + k;
-      const long ka = (gk < k_end) ? kmap(gk) : gk;
-      const bool full = BKC ? (gn < g.N && gk + VB <= k_end && ka + VB <= g.K)
-                            : (gk < k_end && ka < g.K && gn + VB <= g.N);
-      const TB* src = BKC ? B + gn * g.ldb + ka : B + ka * g.ldb + gn;
+      const bool full = BKC ? (gn < g.N && gk + VB <= k_end) : (gk < k_end && gn + VB <= g.N);
+      const TB* src = BKC ? B + gn * g.ldb + gk : B + gk * g.ldb + gn;
       if (vec_b && full) {
         typedef TB vt __attribute__((ext_vector_type(VB)));
         const vt v = *reinterpret_cast<const vt*>(src);
@@ -442,8 +374,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
       } else {
 #pragma unroll
         for (int j = 0; j < VB; ++j) {
-          const bool in = BKC ? (gn < g.N && gk + j < k_end && ka + j < g.K)
-                              : (gk < k_end && ka < g.K && gn + j < g.N);
+          const bool in = BKC ? (gn < g.N && gk + j < k_end) : (gk < k_end && gn + j < g.N);
           rb[r * VB + j] = in ? (CT)src[j] : (CT)0;
         }
       }
@@ -476,39 +407,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
   auto compute = [&](int buf) {
     const CT* a = sA + buf * SLAB_A;
     const CT* b = sB + buf * SLAB_B;
-    if constexpr (MODE == kBF16X3) {
-#pragma unroll
-      for (int ks = 0; ks < BK / 32; ++ks) {
-      const int kq = 32 * ks + 8 * (lane >> 4), rr = lane & 15;
-      bf16x8 ah[MI], al[MI], bh[NJ], bl[NJ];
-#pragma unroll
-      for (int i = 0; i < MI; ++i) {
-        const float* pa = &a[(wm + 16 * i + rr) * PA + kq];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-          __bf16 h, l;
-          split_bf16(pa[v], h, l); ah[i][v] = h; al[i][v] = l;
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const float* pb = &b[(wn + 16 * j + rr) * PB + kq];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-          __bf16 h, l;
-          split_bf16(pb[v], h, l); bh[j][v] = h; bl[j][v] = l;
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int i = 0; i < MI; ++i) {
-          acc[j][i] = mfma_bf16(bl[j], ah[i], acc[j][i]);
-          acc[j][i] = mfma_bf16(bh[j], al[i], acc[j][i]);
-          acc[j][i] = mfma_bf16(bh[j], ah[i], acc[j][i]);
-        }
-      }
-    } else if constexpr (MODE == kBF16) {
+    if constexpr (MODE == kBF16) {
 #pragma unroll
       for (int ks = 0; ks < BK / 32; ++ks) {
       const int kq = 32 * ks + 8 * (lane >> 4), rr = lane & 15;
@@ -529,41 +428,6 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int i = 0; i < MI; ++i) acc[j][i] = mfma_bf16(bh[j], ah[i], acc[j][i]);
-      }
-    } else if constexpr (MODE == kBF16X6) {
-#pragma unroll
-      for (int ks = 0; ks < BK / 32; ++ks) {
-      const int kq = 32 * ks + 8 * (lane >> 4), rr = lane & 15;
-      bf16x8 ah[MI], am[MI], al[MI], bh[NJ], bm[NJ], bl[NJ];
-#pragma unroll
-      for (int i = 0; i < MI; ++i) {
-        const float* pa = &a[(wm + 16 * i + rr) * PA + kq];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-          __bf16 h, m, l;
-          split3_bf16(pa[v], h, m, l); ah[i][v] = h; am[i][v] = m; al[i][v] = l;
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const float* pb = &b[(wn + 16 * j + rr) * PB + kq];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-          __bf16 h, m, l;
-          split3_bf16(pb[v], h, m, l); bh[j][v] = h; bm[j][v] = m; bl[j][v] = l;
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int i = 0; i < MI; ++i) {
-          acc[j][i] = mfma_bf16(bl[j], ah[i], acc[j][i]);
-          acc[j][i] = mfma_bf16(bm[j], am[i], acc[j][i]);
-          acc[j][i] = mfma_bf16(bh[j], al[i], acc[j][i]);
-          acc[j][i] = mfma_bf16(bm[j], ah[i], acc[j][i]);
-          acc[j][i] = mfma_bf16(bh[j], am[i], acc[j][i]);
-          acc[j][i] = mfma_bf16(bh[j], ah[i], acc[j][i]);
-        }
       }
     } else {
 #pragma unroll
@@ -590,23 +454,17 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     // into registers while MFMA runs the current one
     __bf16* pA = reinterpret_cast<__bf16*>(lds_raw);
     __bf16* pB = pA + NP * BM * PKS;
-    constexpr bool APRE = std::is_same<TA, __bf16>::value;
-    static_assert(!APRE || AKC, "pre-split A planes are k-contiguous");
-    const bool va = APRE ? ((reinterpret_cast<uintptr_t>(A) % 16) == 0 && g.lda % 8 == 0 &&
-                            g.a_plane % 8 == 0)
-                         : ((reinterpret_cast<uintptr_t>(A) % (4 * sizeof(TA))) == 0) &&
-                               (g.lda % 4 == 0);
+    const bool va = ((reinterpret_cast<uintptr_t>(A) % (4 * sizeof(TA))) == 0) && (g.lda % 4 == 0);
     constexpr bool BPRE = std::is_same<TB, __bf16>::value;
     static_assert(!BPRE || BKC, "pre-split B planes are k-contiguous");
     const bool vb = BPRE ? ((reinterpret_cast<uintptr_t>(B) % 16) == 0 && g.ldb % 8 == 0 &&
                             g.b_plane % 8 == 0)
                          : ((reinterpret_cast<uintptr_t>(B) % (4 * sizeof(TB))) == 0) &&
                                (g.ldb % 4 == 0);
-    std::conditional_t<APRE, PreSlab<BM, BK, NP>, SplitSlab<TA, CT, BM, BK, AKC>> xa;
+    SplitSlab<TA, CT, BM, BK, AKC> xa;
     std::conditional_t<BPRE, PreSlab<BN, BK, NP>, SplitSlab<TB, CT, BN, BK, BKC>> xb;
-    if constexpr (APRE) xa.plane = g.a_plane;
     if constexpr (BPRE) xb.plane = g.b_plane;
-    long k0 = next_live(k_begin);
+    long k0 = k_begin;
     if (k0 < k_end) {
       xa.load(A, g.lda, m0, g.M, k0, k_end, va, tid);
       xb.load(B, g.ldb, n0, g.N, k0, k_end, vb, tid);
@@ -617,7 +475,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
       xa.template store<NP, PKS>(pA, tid);
       xb.template store<NP, PKS>(pB, tid);
       __syncthreads();
-      const long kn = next_live(k0 + BK);
+      const long kn = k0 + BK;
       if (kn < k_end) {
         xa.load(A, g.lda, m0, g.M, kn, k_end, va, tid);
         xb.load(B, g.ldb, n0, g.N, kn, k_end, vb, tid);
@@ -656,13 +514,13 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     }
   } else {
   // software pipeline: slab t+1 is loaded into registers while slab t runs
-  long k0 = next_live(k_begin);
+  long k0 = k_begin;
   if (k0 < k_end) load_slab(k0);
   int buf = 0;
   while (k0 < k_end) {
     store_slab(buf);
     __syncthreads();
-    const long kn = next_live(k0 + BK);
+    const long kn = k0 + BK;
     if (kn < k_end) load_slab(kn);
     compute(buf);
     buf ^= 1;
@@ -709,15 +567,13 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     // column runs) instead of one value per column
     constexpr int SP = BM + 1, HC = BN / 2;
     float* st = reinterpret_cast<float*>(smem_ab);
-    float* C = (EPI == kPartial) ? (float*)g.C + (long)s * g.M * g.N : (float*)g.C + bidx * g.bs_c;
+    float* C = (EPI == kPartial) ? (float*)g.C + (long)s * g.M * g.N : (float*)g.C;
     const long ldc = (EPI == kPartial) ? (long)g.M : g.ldc;
-    const float* Cin = (EPI == kStore && g.beta != 0.0) ? (const float*)g.Cin + bidx * g.bs_cin
-                                                          : nullptr;
+    const float* Cin = (EPI == kStore && g.beta != 0.0) ? (const float*)g.Cin : nullptr;
     const bool vec_c = (reinterpret_cast<uintptr_t>(C) % 16 == 0) && (ldc % 4 == 0) &&
                        (!Cin || ((reinterpret_cast<uintptr_t>(Cin) % 16 == 0) && g.ldcin % 4 == 0));
-    auto finish = [&](float c_old, float v, long m, long n) -> float {
-      if constexpr (EPI == kAccumulate) return (float)((double)c_old + g.alpha * (double)v);
-      else if constexpr (EPI == kPartial) return v;
+    auto finish = [&](float v, long m, long n) -> float {
+      if constexpr (EPI == kPartial) return v;
       else {
         double out = g.alpha * (double)v;
         if (Cin) out += g.beta * (double)Cin[m + n * g.ldcin];
@@ -780,16 +636,12 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
           continue;
         }
         if (vec_c && m + 4 <= g.M) {
-          float4 cv = make_float4(0.f, 0.f, 0.f, 0.f);
-          if constexpr (EPI == kAccumulate) cv = *reinterpret_cast<const float4*>(cp);
-          cv.x = finish(cv.x, sp[0], m, n);
-          cv.y = finish(cv.y, sp[1], m + 1, n);
-          cv.z = finish(cv.z, sp[2], m + 2, n);
-          cv.w = finish(cv.w, sp[3], m + 3, n);
-          *reinterpret_cast<float4*>(cp) = cv;
+          *reinterpret_cast<float4*>(cp) =
+              make_float4(finish(sp[0], m, n), finish(sp[1], m + 1, n), finish(sp[2], m + 2, n),
+                          finish(sp[3], m + 3, n));
         } else {
           for (int e = 0; e < 4 && m + e < g.M; ++e)
-            cp[e] = finish(EPI == kAccumulate ? cp[e] : 0.f, sp[e], m + e, n);
+            cp[e] = finish(sp[e], m + e, n);
         }
       }
     }
@@ -807,16 +659,10 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
           const double v = to_d(acc[j][i][q]);
           if constexpr (EPI == kPartial) {
             ((TC*)g.C)[(long)s * g.M * g.N + m + n * g.M] = (TC)v;
-          } else if constexpr (EPI == kAccumulate) {
-            TC* C = (TC*)g.C + bidx * g.bs_c;
-            C[m + n * g.ldc] = (TC)(to_d(C[m + n * g.ldc]) + g.alpha * v);
           } else {
-            double out = (g.alpha_dev ? g.alpha * g.alpha_dev[bidx] : g.alpha) * v;
-            if (g.beta != 0.0)
-              out += g.beta * to_d(((const TC*)g.Cin + bidx * g.bs_cin)[m + n * g.ldcin]);
-            ((TC*)g.C + bidx * g.bs_c)[m + n * g.ldc] = (TC)out;
-            if (BM == BN && g.mirror && mt != nt)
-              ((TC*)g.C + bidx * g.bs_c)[n + m * g.ldc] = (TC)out;
+            double out = g.alpha * v;
+            if (g.beta != 0.0) out += g.beta * to_d(((const TC*)g.Cin)[m + n * g.ldcin]);
+            ((TC*)g.C)[m + n * g.ldc] = (TC)out;
           }
         }
   }
@@ -827,12 +673,9 @@ template <int MODE, typename TA, typename TB, bool AKC, bool BKC, int EPI, typen
 inline hipError_t launch_gemm(GemmArgs g, hipStream_t st) {
   constexpr int BM = BT, BN = BN_ > 0 ? BN_ : BT;
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  // the split-at-store modes take a block mask but no k-list
-  if (split_store_mode(MODE) && g.klist) return hipErrorInvalidValue;
   if (g.splits <= 0) g.splits = 1;
   if (g.k_per_split <= 0) g.k_per_split = ((g.K + 63) / 64) * 64;
-  if (g.batch > 1) g.splits = 1;
-  dim3 grid(ceil_div(g.M, BM), ceil_div(g.N, BN), g.batch > 1 ? g.batch : g.splits);
+  dim3 grid(ceil_div(g.M, BM), ceil_div(g.N, BN), g.splits);
   hipLaunchKernelGGL((gemm_kernel<MODE, TA, TB, AKC, BKC, EPI, TC, BM, BN, BK_>), grid, dim3(256), 0,
                      st, g);
   return hipGetLastError();

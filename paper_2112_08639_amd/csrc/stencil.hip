@@ -711,9 +711,9 @@ __global__ __launch_bounds__(MAXT) void stencil_slab_kernel(StencilArgs a) {
 // loads off their alignment are split.  (A thread owning four rows at one x, all accesses
 // single elements, spilled: 255 us at 45 x 40 x 54 x 203.)
 // LDS pitch of a row: its length, kPad copies at either end, a multiple that leaves sixteen
-// waves of narrow planes room in LDS (nx <= 32: 48, else 96)
-constexpr int rows_pitch(int nx) { return nx <= 32 ? 48 : 96; }
-constexpr int kRowsMaxNx = 80;
+// waves of narrow planes room in LDS (nx <= 32: 48, <= 80: 96, else 128)
+constexpr int rows_pitch(int nx) { return nx <= 32 ? 48 : nx <= 80 ? 96 : 128; }
+constexpr int kRowsMaxNx = 112;
 
 template <typename T, int W>
 __device__ __forceinline__ VecW<T, W> ldu(const T* p) {
@@ -1013,19 +1013,23 @@ static hipError_t launch_rows(StencilArgs a, const RowsPlan& p, int n_s, hipStre
   a.ty_tile = p.ty;
   a.zc = p.zc;
   const size_t smem = rows_lds_bytes(a.nx, p.ty, sizeof(T));
-  const bool narrow = rows_pitch(a.nx) == 48;
-  const auto kernel =
-      p.slabs == 1 ? (narrow ? stencil_rows_kernel<T, W, R, true, 48>
-                             : stencil_rows_kernel<T, W, R, true, 96>)
-                   : (narrow ? stencil_rows_kernel<T, W, R, false, 48>
-                             : stencil_rows_kernel<T, W, R, false, 96>);
-  if (smem > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute((const void*)kernel,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(kernel, dim3(p.slabs, p.chunks, n_s), dim3(p.threads), smem, st, a);
-  return hipGetLastError();
+  auto launch = [&](auto kernel) -> hipError_t {
+    if (smem > 64 * 1024) {
+      const hipError_t e = hipFuncSetAttribute(
+          (const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kernel, dim3(p.slabs, p.chunks, n_s), dim3(p.threads), smem, st, a);
+    return hipGetLastError();
+  };
+  const int pitch = rows_pitch(a.nx);
+  if (p.slabs == 1)
+    return pitch == 48   ? launch(stencil_rows_kernel<T, W, R, true, 48>)
+           : pitch == 96 ? launch(stencil_rows_kernel<T, W, R, true, 96>)
+                         : launch(stencil_rows_kernel<T, W, R, true, 128>);
+  return pitch == 48   ? launch(stencil_rows_kernel<T, W, R, false, 48>)
+         : pitch == 96 ? launch(stencil_rows_kernel<T, W, R, false, 96>)
+                       : launch(stencil_rows_kernel<T, W, R, false, 128>);
 }
 
 template <typename T, int PPT>
@@ -1084,10 +1088,17 @@ hipError_t stencil_step(dk_ctx* c, const void* yin, const void* yprev, void* you
       return hipGetLastError();
     }
   }
+  // Rows kernel up to 112 points a row.  Above 80, FP32 planes that need several of its
+  // workgroups and that the slab kernel takes stay there: it loads the halo rows a plane
+  // ahead (96^3 x 512: 1592 against 1829 us; 112 x 64 x 64 x 200: 388 and 384 us).  Planes
+  // of one workgroup, rows off the vectors and FP64 gain (96 x 40 x 40 x 300: 188 -> 146 us;
+  // 90^3 x 200: 1863 -> 783 us; 81 x 40 x 50 x 300: 662 -> 344 us; FP64 96^3 x 128: 890 ->
+  // 687 us, 99 x 50 x 40 x 100: 302 -> 175 us; times of one application)
   if (c->nx <= kRowsMaxNx) {
     const int W = f64 ? 2 : 4;
     const RowsPlan p = plan_rows(c->nx, c->ny, c->nz, n_s, W);
-    if (p.slabs > 0) {
+    const bool slab = !f64 && c->nx > 80 && p.slabs > 1 && c->nx % 4 == 0 && ld % 4 == 0;
+    if (p.slabs > 0 && !slab) {
       const int R = c->nx % W;
       if (f64)
         return R == 0 ? launch_rows<double, 2, 0>(a, p, n_s, c->stream)

@@ -1,6 +1,6 @@
 """H X where the local part's row kernel has edges: row lengths on both sides of its vectors
-(four points in FP32, two in FP64), of its two LDS pitches (32, 33) and of its last row
-length (80, 81), the smallest grid, slabs whose last one is shorter, planes of one slab,
+(four points in FP32, two in FP64), of its three LDS pitches (32, 33, 80, 81) and of its
+last row length (112, 113), the smallest grid, slabs whose last one is shorter, planes of one slab,
 z-chunks of unequal length, odd leading dimensions.  Oracle: the FP64 Hamiltonian;
 tolerances as for H X elsewhere (FP64 1e-12, FP32 blocks 2e-5)."""
 
@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 H0 = 0.32
 DIMS = [(7, 7, 7), (8, 9, 10), (9, 7, 25), (10, 30, 8), (11, 13, 17), (12, 25, 19),
         (31, 14, 9), (32, 40, 13), (33, 41, 12), (34, 26, 11), (48, 48, 14), (63, 50, 9),
-        (80, 31, 8), (81, 16, 9)]
+        (80, 31, 8), (81, 16, 9), (96, 21, 8), (96, 52, 8), (112, 16, 9), (113, 14, 8)]
 
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])

@@ -122,9 +122,11 @@ __global__ __launch_bounds__(256) void dense_rows_kernel(const int* __restrict__
 // further waves of the workgroup only move them, several stages ahead in registers: a
 // wave's memory operations complete in order, so a consumer that loaded them would wait
 // for its tile of the next block as well (373248 x 2048, 432 projectors, two pieces: 1.60
-// against 1.16 ms).  Measured: 66 us at 110592 x 512 over 128 projectors (3.4 TB/s), before 80
-// over the dense table; 1.10 against 1.72 ms at 373248 x 2048; FP64 274 against 342 us
-// at 110592 x 512, bound by MFMA on row blocks of which half the slots are live.  In the
+// against 1.16 ms).  Measured: 60 us at 110592 x 512 over 128 projectors (3.8 TB/s), before 80
+// over the dense table; 1.10 against 1.72 ms at 373248 x 2048; FP64 246 against 342 us
+// at 110592 x 512, bound by MFMA on row blocks of which two thirds of the slots are live
+// (133 us without the products, 237 us without the block; table values read a quarter of a
+// row block ahead, 253 against 254 us).  In the
 // mixed kernel the feeding waves run at the highest priority (64.6 -> 62.8 us and, over
 // 432 projectors, 1.23 -> 1.17 ms); in FP64, where they share SIMDs whose matrix pipes are
 // full, at the same as the others (higher: 272 -> 297 us).

@@ -46,6 +46,11 @@ inline int ceil_div(long a, long b) { return int((a + b - 1) / b); }
 __device__ __forceinline__ f64x4 mfma_f64(double a, double b, f64x4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
+// four 4x4x4 products side by side, block b = lane / 4 % 4: lane supplies
+// A_b[lane % 4][lane / 16] and B_b[lane / 16][lane % 4], holds D_b[lane / 16][lane % 4]
+__device__ __forceinline__ double mfma_f64_4(double a, double b, double c) {
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
 
 // Same shape, FP32: register r of lane l holds D[4*(l/16) + r][l%16].
 __device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {

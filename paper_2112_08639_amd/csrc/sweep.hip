@@ -123,13 +123,10 @@ __global__ __launch_bounds__(256) void dense_rows_kernel(const int* __restrict__
 // wave's memory operations complete in order, so a consumer that loaded them would wait
 // for its tile of the next block as well (373248 x 2048, 432 projectors, two pieces: 1.60
 // against 1.16 ms).  Measured: 60 us at 110592 x 512 over 128 projectors (3.8 TB/s), before 80
-// over the dense table; 1.10 against 1.72 ms at 373248 x 2048; FP64 246 against 342 us
-// at 110592 x 512, bound by MFMA on row blocks of which two thirds of the slots are live
-// (133 us without the products, 237 us without the block; table values read a quarter of a
-// row block ahead, 253 against 254 us).  In the
-// mixed kernel the feeding waves run at the highest priority (64.6 -> 62.8 us and, over
-// 432 projectors, 1.23 -> 1.17 ms); in FP64, where they share SIMDs whose matrix pipes are
-// full, at the same as the others (higher: 272 -> 297 us).
+// over the dense table; 1.10 against 1.72 ms at 373248 x 2048; FP64 186 against 342 us
+// at 110592 x 512.  In the mixed kernel the feeding waves run at the highest priority
+// (64.6 -> 62.8 us and, over 432 projectors, 1.23 -> 1.17 ms); in FP64, where they share
+// SIMDs whose matrix pipes are full, at the same as the others (higher: 186 -> 208 us).
 
 constexpr int kFeedWaves = 4;
 constexpr int kFeedDepth = 2;
@@ -361,18 +358,24 @@ void integrals_mixed_kernel(SweepArgs a) {
       }
 }
 
-// FP64, one 16-column block per wave.  MFMA 16x16x4 f64: lane l supplies A[l%16][l/16],
-// B[l/16][l%16]; register r holds D[l/16 + 4r][l%16].
-template <int RB, int CW>
+// FP64, one 16-column block per wave, one product of four projectors at a time: the four
+// 4x4x4 blocks of the MFMA are four columns each, with the same projectors.  Only live
+// slots are multiplied, where 16x16x4 works on four slots as soon as one is live (6.4 of 8
+// row blocks at 48^3 over 32 groups, of which 16 are live); both forms run at the same
+// rate (65 and 66 TFLOP/s from registers).  110592 x 512: 254 -> 186 us, 373248 x 512 over
+// 432 projectors 1.10 -> 0.91 ms, 64000 x 300: 139 -> 120 us.  What bounds it now is the LDS
+// path as much as the products (156 us with multiply-adds in their place): a lane needs
+// all 16 points of its projector and k for every 16 columns.  Lane (g, column c16):
+// SLOTS accumulators, acc[s] projector g of slot s.
+template <int SLOTS, int CW>
 __global__ __launch_bounds__(64 * (CW + kFeedWaves), (CW + kFeedWaves) / 4)
 void integrals_f64_kernel(SweepArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char sweep_lds[];
   constexpr int BUF = kF64Units * kStageEntries;
-  static_assert(4 * RB <= kStageEntries, "one stage per block");
+  static_assert(SLOTS <= kStageEntries && SLOTS <= 32, "one stage per block");
   f32x4* const ring = reinterpret_cast<f32x4*>(sweep_lds);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, c16 = lane & 15;
-  const unsigned slot_bit = 1u << (c16 >> 2), slot_below = slot_bit - 1;
   const long w = xcd_work_item(blockIdx.x, (long)gridDim.x);
   const SweepRun run(a, (int)(w / a.ntiles));
   if (wave >= CW) {
@@ -414,9 +417,9 @@ void integrals_f64_kernel(SweepArgs a) {
   };
   const int first = next_live(0);
   if (active && first < run.nb) load_x(first);
-  f64x4 acc[RB];
+  double acc[SLOTS];
 #pragma unroll
-  for (int b = 0; b < RB; ++b) acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
+  for (int s = 0; s < SLOTS; ++s) acc[s] = 0.0;
   __syncthreads();
   int buf = 0, barriers = 1;
   for (int t = first; t < run.nb;) {
@@ -432,23 +435,19 @@ void integrals_f64_kernel(SweepArgs a) {
     if (active) {
       const double* const tab = reinterpret_cast<const double*>(ring + buf * BUF);
 #pragma unroll
-      for (int b = 0; b < RB; ++b) {
-        const unsigned nib = (live >> (4 * b)) & 15u;
-        if (nib == 0) continue;
-        const int at = (int)__popc(live & ((1u << (4 * b)) - 1)) + (int)__popc(nib & slot_below);
-        const bool on = (nib & slot_bit) != 0;
+      for (int s = 0; s < SLOTS; ++s) {
+        if (((live >> s) & 1u) == 0) continue;
+        const int at = (int)__popc(live & ((1u << s) - 1));
         const double* const tp = tab + min(at, kStageEntries - 1) * kF64Elems +
                                  f64_at(e0 + at, 0, c16 & 3, g, 0);
 #pragma unroll
         for (int mb = 0; mb < 4; ++mb) {
           f64x2_t tv[2];
 #pragma unroll
-          for (int h = 0; h < 2; ++h) {
+          for (int h = 0; h < 2; ++h)
             tv[h] = *reinterpret_cast<const f64x2_t*>(tp + 64 * mb + 32 * h);
-            if (!on) tv[h] = f64x2_t{0.0, 0.0};
-          }
 #pragma unroll
-          for (int r = 0; r < 4; ++r) acc[b] = mfma_f64(tv[r >> 1][r & 1], z[mb][r], acc[b]);
+          for (int r = 0; r < 4; ++r) acc[s] = mfma_f64_4(tv[r >> 1][r & 1], z[mb][r], acc[s]);
         }
       }
     }
@@ -460,14 +459,9 @@ void integrals_f64_kernel(SweepArgs a) {
   for (; barriers % kFeedDepth != 0; ++barriers) __syncthreads();
   if (!active) return;
   double* __restrict__ part = (double*)a.part + (long)4 * run.uoff * a.n_s;
-  const int rows = 4 * run.ulen;
 #pragma unroll
-  for (int b = 0; b < RB; ++b)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = 16 * b + g + 4 * i;
-      if (r < rows) part[(long)r * a.n_s + col] = acc[b][i];
-    }
+  for (int s = 0; s < SLOTS; ++s)
+    if (s < run.ulen) part[(long)(4 * s + g) * a.n_s + col] = acc[s];
 }
 
 // ----------------------------------------------------------------- scatter --
@@ -732,13 +726,12 @@ __global__ __launch_bounds__(256) void group_lists_kernel(const double* __restri
   }
 }
 
-// Order of the groups.  The integrals work on row blocks of four consecutive groups, all
-// of it if one of them is live, so groups that are live in the same blocks are put next to
-// each other: a block is (part of) an x-row, so they are sorted by the z of their centre
-// in layers of kLayer bohr, then by y.  With atoms in the order of cubic cells 6.7 of 8 row blocks
-// are live at 48^3 over 32 groups and 9.9 of 16 at 72^3 over 108; sorted, 5.3 and 7.5, and
-// the integrals of 512 columns (FP64) take 249 instead of 272 us, of 2048 columns (mixed)
-// 1.10 instead of 1.17 ms.
+// Order of the groups.  The mixed integrals work on row blocks of four consecutive groups,
+// all of it if one of them is live, so groups that are live in the same blocks are put next
+// to each other: a block is (part of) an x-row, so they are sorted by the z of their centre
+// in layers of kLayer bohr, then by y.  With atoms in the order of cubic cells 6.7 of 8 row
+// blocks are live at 48^3 over 32 groups and 9.9 of 16 at 72^3 over 108; sorted, 5.3 and
+// 7.5, and the integrals of 2048 columns take 1.10 instead of 1.17 ms.
 // From here on a group is its place in that order, perm[place] the four projectors and
 // ggamma their energies.
 constexpr double kLayer = 4.0;
@@ -1143,7 +1136,7 @@ hipError_t nonlocal_integrals(dk_ctx* c, const void* x, long ld, int n_s, double
   KTimer kt(c, DK_K_NL_GATHER);
   hipError_t e;
   if (c->precision == DK_PREC_FP64)
-    e = launch_integrals(integrals_f64_kernel<8, kConsumers>, a, p, kF64Units, 0, c->stream);
+    e = launch_integrals(integrals_f64_kernel<32, kConsumers>, a, p, kF64Units, 0, c->stream);
   else if (subspace) e = integrals_mixed<2>(a, p, c->stream);
   else e = integrals_mixed<3>(a, p, c->stream);
   if (e != hipSuccess) return e;

@@ -656,14 +656,14 @@ __global__ __launch_bounds__(256, OCC) void scatter_kernel(ScatterArgs a) {
 
 // coef[(group n_s + col) 4 + p] = scale rowscale[4 group + p] sum over the runs that hold
 // the group of the partial row (4 occ + p); zero past the last projector.  A workgroup
-// takes one projector and 64 columns; its four waves sum interleaved quarters of the
+// takes one projector and 64 columns; its W waves sum interleaved shares of the
 // occurrences, kReduceDepth loads in flight each, which is what the time goes by
-// (two in flight: 12 us at 24^3 x 64 in FP64, 10 at 48^3 x 512 mixed; now 6 and 7; at 72^3 x
+// (two in flight: 12 us at 24^3 x 64 in FP64, 10 at 48^3 x 512 mixed; now 4 and 7; at 72^3 x
 // 2048 mixed, 108 groups, both 80, bound by the partials).  occ null: the dense runs,
 // occurrence o of group g = o n_groups + g.
 constexpr int kReduceDepth = 16;
-template <typename PT>
-__global__ __launch_bounds__(256) void sweep_reduce_kernel(const PT* __restrict__ part, int n_s,
+template <typename PT, int W>
+__global__ __launch_bounds__(64 * W) void sweep_reduce_kernel(const PT* __restrict__ part, int n_s,
                                                            int n_proj, int n_groups, int n_runs,
                                                            const int* __restrict__ occ_off,
                                                            const int* __restrict__ occ,
@@ -671,7 +671,7 @@ __global__ __launch_bounds__(256) void sweep_reduce_kernel(const PT* __restrict_
                                                            double scale,
                                                            const double* __restrict__ rowscale,
                                                            PT* __restrict__ out) {
-  __shared__ double sh[4][64];
+  __shared__ double sh[W][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int grp = blockIdx.x >> 2, p = blockIdx.x & 3;
   const int proj = 4 * perm[grp] + p;
@@ -680,22 +680,25 @@ __global__ __launch_bounds__(256) void sweep_reduce_kernel(const PT* __restrict_
   const int o0 = occ ? occ_off[grp] : 0, o1 = occ ? occ_off[grp + 1] : n_runs;
   double acc = 0.0;
   if (col < n_s) {
-    for (int o = o0 + wv; o < o1; o += 4 * kReduceDepth) {
+    for (int o = o0 + wv; o < o1; o += W * kReduceDepth) {
       PT v[kReduceDepth];
 #pragma unroll
       for (int i = 0; i < kReduceDepth; ++i) {
-        const int oi = min(o + 4 * i, o1 - 1);
+        const int oi = min(o + W * i, o1 - 1);
         v[i] = part[(4L * (occ ? occ[oi] : (long)oi * n_groups + grp) + p) * n_s + col];
       }
 #pragma unroll
       for (int i = 0; i < kReduceDepth; ++i)
-        if (o + 4 * i < o1) acc += (double)v[i];
+        if (o + W * i < o1) acc += (double)v[i];
     }
   }
   sh[wv][lane] = acc;
   __syncthreads();
   if (wv == 0 && col < n_s) {
-    const double s = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < W; w += 4)
+      s += (sh[w][lane] + sh[w + 1][lane]) + (sh[w + 2][lane] + sh[w + 3][lane]);
     out[((long)grp * n_s + col) * 4 + p] = proj < n_proj ? (PT)(s * scale * rs) : (PT)0;
   }
 }
@@ -1144,14 +1147,24 @@ hipError_t nonlocal_integrals(dk_ctx* c, const void* x, long ld, int n_s, double
   const int* off = dense ? nullptr : c->gocc_off;
   const int* occ = dense ? nullptr : c->gocc;
   const double scale = c->dv * alpha;
-  if (c->precision == DK_PREC_MIXED)
-    hipLaunchKernelGGL(sweep_reduce_kernel<float>, grid, dim3(256), 0, c->stream,
-                       (const float*)w.part, n_s, c->n_proj, c->n_groups, p.n_runs, off, occ,
-                       c->gperm, scale, c->ggamma, (float*)w.coef);
-  else
-    hipLaunchKernelGGL(sweep_reduce_kernel<double>, grid, dim3(256), 0, c->stream,
-                       (const double*)w.part, n_s, c->n_proj, c->n_groups, p.n_runs, off, occ,
-                       c->gperm, scale, c->ggamma, (double*)w.coef);
+  auto reduce = [&](auto kernel, auto* part, auto* out, int waves) {
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), 0, c->stream, part, n_s, c->n_proj,
+                       c->n_groups, p.n_runs, off, occ, c->gperm, scale, c->ggamma, out);
+  };
+  // sixteen waves where four need more than one round of loads and the workgroups leave a
+  // CU each (216 runs, 16 workgroups: 6.0 -> 4.1 us; with 512 workgroups over 128 runs the
+  // second round of workgroups takes back what the round of loads gave)
+  const long occurrences = dense ? p.n_runs : c->g_rows / c->n_groups;
+  const bool wide = occurrences > 4 * kReduceDepth && (long)grid.x * grid.y <= 256;
+  if (c->precision == DK_PREC_MIXED) {
+    const float* part = (const float*)w.part;
+    if (wide) reduce(sweep_reduce_kernel<float, 16>, part, (float*)w.coef, 16);
+    else reduce(sweep_reduce_kernel<float, 4>, part, (float*)w.coef, 4);
+  } else {
+    const double* part = (const double*)w.part;
+    if (wide) reduce(sweep_reduce_kernel<double, 16>, part, (double*)w.coef, 16);
+    else reduce(sweep_reduce_kernel<double, 4>, part, (double*)w.coef, 4);
+  }
   return hipGetLastError();
 }
 

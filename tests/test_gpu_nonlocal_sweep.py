@@ -2,8 +2,8 @@
 grids that are no multiple of the 64-point blocks, odd leading dimensions,
 blocks of 1, 17 and 130 columns, one group, the last group counts of the dense
 runs (32 and 64 groups) and the first of the compact ones (65 and more live
-groups in a block), a cell with points no projector reaches.  Oracle: the FP64
-Hamiltonian; tolerances as for H X elsewhere (FP64 1e-12, FP32 blocks 2e-5)."""
+groups in a block), a cell with points no projector reaches, and run counts on both sides
+of the reduction's two widths (64 and fewer, 167, 216).  Oracle: the FP64 Hamiltonian; tolerances as for H X elsewhere (FP64 1e-12, FP32 blocks 2e-5)."""
 
 import numpy as np
 import pytest
@@ -21,6 +21,8 @@ CASES = [("one", 6.0, 1, 13, "sc", 17),         # one atom, 2197 points
          ("g27", 4.0, 3, 17, "sc", 130),
          ("g32", 5.0, 2, 14, "fcc", 33),        # the dense runs' last count in FP64
          ("g64", 3.5, 4, 15, "sc", 70),         # and in the mixed path
+         ("r64", 5.0, 1, 16, "fcc", 5),         # runs of one block: 64 of them
+         ("r167", 7.0, 1, 22, "fcc", 65),
          ("g108", 4.5, 3, 19, "fcc", 18)]
 
 

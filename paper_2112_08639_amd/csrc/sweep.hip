@@ -741,14 +741,19 @@ constexpr double kLayer = 4.0;
 constexpr int kOrderMax = 1024;  // groups; beyond, the order stays as it is
 
 // centres (circular means over the live blocks) as fixed-point sums, whose order does not
-// matter: sums[4 g + {0, 1}] of cos, sin of z, {2, 3} of y
+// matter: sums[4 g + {0, 1}] of cos, sin of z, {2, 3} of y.  At most kOrderMax groups; each
+// workgroup sums in LDS first (every wave adding to the same few counters in memory: 118 us
+// at 48^3 over 32 groups)
 __global__ __launch_bounds__(256) void group_centres_kernel(const int* __restrict__ klist,
                                                             const int* __restrict__ kcount,
                                                             int nblocks, int n_groups, int nx,
                                                             int ny, int nz,
                                                             unsigned long long* __restrict__ sums) {
+  __shared__ unsigned long long own[4 * kOrderMax];
   const int lane = threadIdx.x & 63;
   const int nwaves = (gridDim.x * 256) >> 6;
+  for (int i = threadIdx.x; i < 4 * n_groups; i += 256) own[i] = 0;
+  __syncthreads();
   for (int b = (blockIdx.x * 256 + threadIdx.x) >> 6; b < nblocks; b += nwaves) {
     const long e = min((long)b * 64 + 32, (long)nx * ny * nz - 1);
     const int y = (int)((e / nx) % ny), z = (int)(e / ((long)nx * ny));
@@ -757,9 +762,12 @@ __global__ __launch_bounds__(256) void group_centres_kernel(const int* __restric
     sincospi(2.0 * y / ny, &v[3], &v[2]);
     for (int i = lane; i < kcount[b]; i += 64)
       for (int k = 0; k < 4; ++k)
-        atomicAdd(sums + 4 * klist[(long)b * n_groups + i] + k,
+        atomicAdd(own + 4 * klist[(long)b * n_groups + i] + k,
                   (unsigned long long)(long long)rint(v[k] * (1 << 20)));
   }
+  __syncthreads();
+  for (int i = threadIdx.x; i < 4 * n_groups; i += 256)
+    if (own[i] != 0) atomicAdd(sums + i, own[i]);
 }
 
 __global__ __launch_bounds__(1024) void group_order_kernel(
@@ -1061,11 +1069,13 @@ hipError_t build_sweep_tables(dk_ctx* c) {
   hipLaunchKernelGGL(group_lists_kernel, dim3((int)blocks), dim3(256), 0, c->stream, c->chi64,
                      c->ngrid, c->n_proj, nb, n_groups, c->klist, c->kcount);
   int* const rank = c->gperm + n_groups;
-  if ((e = hipMemsetAsync(c->gcentre, 0, 4 * (size_t)n_groups * sizeof(unsigned long long),
-                          c->stream)) != hipSuccess)
-    return e;
-  hipLaunchKernelGGL(group_centres_kernel, dim3(64), dim3(256), 0, c->stream, c->klist, c->kcount,
-                     (int)nb, n_groups, c->nx, c->ny, c->nz, c->gcentre);
+  if (n_groups <= kOrderMax) {
+    if ((e = hipMemsetAsync(c->gcentre, 0, 4 * (size_t)n_groups * sizeof(unsigned long long),
+                            c->stream)) != hipSuccess)
+      return e;
+    hipLaunchKernelGGL(group_centres_kernel, dim3(64), dim3(256), 0, c->stream, c->klist,
+                       c->kcount, (int)nb, n_groups, c->nx, c->ny, c->nz, c->gcentre);
+  }
   hipLaunchKernelGGL(group_order_kernel, dim3(1), dim3(1024), 0, c->stream, c->gcentre, n_groups,
                      c->ly, c->lz, c->gamma_dev, c->n_proj, c->gperm, rank, c->ggamma);
   if (n_groups <= kOrderMax)

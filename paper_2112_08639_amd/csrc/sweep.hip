@@ -8,7 +8,7 @@
 // Precision.  Mixed: the scatter is FP32 MFMA with the sum over projectors kept apart
 // from Y and added once; the integrals are split-BF16 with FP32 accumulation over at
 // most 64 blocks (three pieces, six products: FP32 level; two pieces, three products in
-// the filter steps).  FP64: FP64 MFMA throughout.
+// the filter steps over more than kFullProj projectors).  FP64: FP64 MFMA throughout.
 #include <algorithm>
 #include <vector>
 
@@ -21,6 +21,11 @@ namespace dk {
 namespace {
 
 constexpr int kMaxRunBlocks = 64;  // FP32 accumulation: at most 64 blocks of 64 points
+// Up to this many projectors the filter steps take FP32-level products as well: two pieces
+// are off by 2^-18 of each product (H X where the nonlocal term dominates: 4e-6 of its rms,
+// three pieces 1e-7), and so few projectors are a small part of a step (16 atoms, 55296 x
+// 512, 8 steps: 1.26 ms with two pieces, 1.38 with three, 1.60 on FP32 MFMA).
+constexpr int kFullProj = 64;
 
 // ------------------------------------------------------------- the tables --
 
@@ -1128,7 +1133,8 @@ hipError_t nonlocal_integrals(dk_ctx* c, const void* x, long ld, int n_s, double
   if (c->n_proj == 0 || n_s <= 0) return hipSuccess;
   const SweepWs w = sweep_ws(c, n_s, ws);
   if (!w.ok) return hipErrorInvalidValue;
-  const SweepPlan p = plan_sweep(c, n_s, subspace);
+  const bool two_piece = subspace && c->n_proj > kFullProj;
+  const SweepPlan p = plan_sweep(c, n_s, two_piece);
   const bool dense = dense_runs(c);
   SweepArgs a{};
   a.x = x;
@@ -1150,7 +1156,7 @@ hipError_t nonlocal_integrals(dk_ctx* c, const void* x, long ld, int n_s, double
   hipError_t e;
   if (c->precision == DK_PREC_FP64)
     e = launch_integrals(integrals_f64_kernel<32, kConsumers>, a, p, kF64Units, 0, c->stream);
-  else if (subspace) e = integrals_mixed<2>(a, p, c->stream);
+  else if (two_piece) e = integrals_mixed<2>(a, p, c->stream);
   else e = integrals_mixed<3>(a, p, c->stream);
   if (e != hipSuccess) return e;
   const dim3 grid(4 * c->n_groups, ceil_div(n_s, 64));

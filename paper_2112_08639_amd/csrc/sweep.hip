@@ -20,7 +20,17 @@ namespace dk {
 
 namespace {
 
-constexpr int kMaxRunBlocks = 64;  // FP32 accumulation: at most 64 blocks of 64 points
+// FP32 accumulation.  Runs take at most 64 blocks of 64 points.  Each block's products are
+// summed apart and added to the run's sum once (otherwise a sum that grows with the run is
+// rounded 12 times per block: the error of H X over 128 projectors at 110592 x 2048, runs of
+// 54 blocks, is 4.8e-7 of its rms where the nonlocal term dominates, against 1.8e-7).  Two
+// pieces are off by 4e-6 there, and sums apart cost registers that their widest kernel does
+// not have (2.70 against 2.79 ms for 8 filter steps at 110592 x 512): they sum straight on
+// where runs are short, at most kPlainBlocks in equal shares and kMaxChunkBlocks over
+// compact supports.
+constexpr int kMaxRunBlocks = 64;
+constexpr int kPlainBlocks = 14;
+constexpr int kMaxChunkBlocks = 32;
 // Up to this many projectors the filter steps take FP32-level products as well: two pieces
 // are off by 2^-18 of each product (H X where the nonlocal term dominates: 4e-6 of its rms,
 // three pieces 1e-7), and so few projectors are a small part of a step (16 atoms, 55296 x
@@ -192,8 +202,8 @@ constexpr int piece_units(int NP) { return 32 * NP; }
 constexpr int kF64Units = kF64Elems / 2;
 
 // RB: 16-projector row blocks of the run's union (4 slots each), CB: 16-column blocks per
-// wave, CW consumer waves, NP bf16 pieces.
-template <int RB, int CB, int CW, int NP>
+// wave, CW consumer waves, NP bf16 pieces; APART: each block's sum apart from the run's.
+template <int RB, int CB, int CW, int NP, bool APART>
 __global__ __launch_bounds__(64 * (CW + kFeedWaves), (CW + kFeedWaves) / 4)
 void integrals_mixed_kernel(SweepArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char sweep_lds[];
@@ -331,19 +341,26 @@ void integrals_mixed_kernel(SweepArgs a) {
         for (int ks = 0; ks < 2; ++ks)
           tv[p][ks] = *reinterpret_cast<const bf16x8*>(tp + 256 * p + 128 * ks);
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
+      for (int cb = 0; cb < CB; ++cb) {
+        // smallest products first
+        f32x4 v = APART ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[b][cb];
+        if constexpr (NP == 3) {
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-          f32x4 v = acc[b][cb];
-          if constexpr (NP == 3) {  // smallest products first
+          for (int ks = 0; ks < 2; ++ks) {
             v = mfma_bf16(tv[NP - 1][ks], xb[0][ks][cb], v);
             v = mfma_bf16(tv[1][ks], xb[1][ks][cb], v);
             v = mfma_bf16(tv[0][ks], xb[NP - 1][ks][cb], v);
           }
+        }
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
           v = mfma_bf16(tv[1][ks], xb[0][ks][cb], v);
           v = mfma_bf16(tv[0][ks], xb[1][ks][cb], v);
-          acc[b][cb] = mfma_bf16(tv[0][ks], xb[0][ks][cb], v);
         }
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) v = mfma_bf16(tv[0][ks], xb[0][ks][cb], v);
+        acc[b][cb] = APART ? acc[b][cb] + v : v;
+      }
     }
     next_stage();
   }
@@ -837,6 +854,7 @@ struct SweepPlan {
   int rb = 8, cb = 1;
   int n_runs = 0, run_len = 0, ntiles = 0;
   long rows = 0;  // partial rows
+  bool apart = false;  // two pieces: sums apart
 };
 
 SweepPlan plan_sweep(const dk_ctx* c, int n_s, bool two_piece) {
@@ -857,6 +875,7 @@ SweepPlan plan_sweep(const dk_ctx* c, int n_s, bool two_piece) {
   if (runs < 1) runs = 1;
   long len = (nb + runs - 1) / runs;
   if (len > kMaxRunBlocks) len = kMaxRunBlocks;
+  p.apart = len > kPlainBlocks;
   p.run_len = (int)len;
   p.n_runs = (int)((nb + len - 1) / len);
   p.rows = 4L * c->n_groups * p.n_runs;
@@ -894,12 +913,20 @@ hipError_t integrals_mixed(const SweepArgs& a, const SweepPlan& p, hipStream_t s
   // the consumers' tiles and the zero entry
   const size_t tiles = (size_t)kConsumers * p.cb * NP * 16 * kTilePitch * sizeof(__bf16) +
                        units * sizeof(f32x4);
-  if (p.rb == 16)
-    return launch_integrals(integrals_mixed_kernel<16, 1, kConsumers, NP>, a, p, units, tiles, st);
-  if constexpr (NP == 2)
+  auto go = [&](auto kernel) { return launch_integrals(kernel, a, p, units, tiles, st); };
+  if constexpr (NP == 3) {
+    return p.rb == 16 ? go(integrals_mixed_kernel<16, 1, kConsumers, 3, true>)
+                      : go(integrals_mixed_kernel<8, 1, kConsumers, 3, true>);
+  } else {
+    if (p.rb == 16)
+      return p.apart ? go(integrals_mixed_kernel<16, 1, kConsumers, 2, true>)
+                     : go(integrals_mixed_kernel<16, 1, kConsumers, 2, false>);
     if (p.cb == 2)
-      return launch_integrals(integrals_mixed_kernel<8, 2, kConsumers, NP>, a, p, units, tiles, st);
-  return launch_integrals(integrals_mixed_kernel<8, 1, kConsumers, NP>, a, p, units, tiles, st);
+      return p.apart ? go(integrals_mixed_kernel<8, 2, kConsumers, 2, true>)
+                     : go(integrals_mixed_kernel<8, 2, kConsumers, 2, false>);
+    return p.apart ? go(integrals_mixed_kernel<8, 1, kConsumers, 2, true>)
+                   : go(integrals_mixed_kernel<8, 1, kConsumers, 2, false>);
+  }
 }
 
 struct SweepWs {
@@ -992,7 +1019,7 @@ hipError_t build_chunks(dk_ctx* c) {
     }
     int fresh = 0;
     for (int i = 0; i < n; ++i) fresh += slot_of[live[i]] < 0;
-    if (cur_n > 0 && ((long)(uni.size() - uoff) + fresh > umax || cur_n >= kMaxRunBlocks)) close();
+    if (cur_n > 0 && ((long)(uni.size() - uoff) + fresh > umax || cur_n >= kMaxChunkBlocks)) close();
     if (cur_n == 0) cur_begin = (int)b;
     for (int i = 0; i < n; ++i)
       if (slot_of[live[i]] < 0) {

@@ -46,9 +46,11 @@ def _apply(n, reps, channels, n_s, precision, X, filtered):
         ctx.close()
 
 
-def _error(n, reps, channels, n_s, filtered):
-    X = torch.randn((n_s, n[0] * n[1] * n[2]), generator=torch.Generator().manual_seed(n_s))
-    X = X.cuda()
+def _error(n, reps, channels, n_s, filtered, positive=False):
+    X = torch.randn((n_s, n[0] * n[1] * n[2]), device="cuda",
+                    generator=torch.Generator("cuda").manual_seed(n_s))
+    if positive:
+        X.abs_().add_(0.5)
     ref = _apply(n, reps, channels, n_s, "fp64", X, filtered)
     got = _apply(n, reps, channels, n_s, "mixed", X, filtered)
     return math.sqrt(float((got - ref).square().sum() / ref.square().sum()))
@@ -66,3 +68,10 @@ SP = ((0, 1.2, 1e5), (1, 1.4, -6e4))
                                                  ((40, 40, 20), (4, 4, 1), SP, 64)])
 def test_fp32_level_up_to_64_projectors(n, reps, channels, n_s, filtered):
     assert _error(n, reps, channels, n_s, filtered) < 1e-6
+
+
+# Runs of 63 blocks of 64 points.  Rounded once a block, the sums of a run leave 0.4 2^-24
+# sqrt(63 / 2) = 1.3e-7, together with the FP32 roundings of the rest (2e-7) 2.4e-7; rounded
+# at each of a block's twelve products, 0.4 2^-24 sqrt(12 63 / 2) = 4.6e-7.
+def test_long_runs():
+    assert _error((40, 40, 40), (4, 4, 2), SP, 2048, False) < 3.5e-7

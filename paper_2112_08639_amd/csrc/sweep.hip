@@ -60,10 +60,10 @@ __global__ __launch_bounds__(256) void sweep_table_kernel(
       return (x < ngrid && proj < n_proj) ? chi[(long)proj * ngrid + x] : 0.0;
     };
     if constexpr (MIXED) {
-      // scatter operand: projector g, points 4 r16 ..
+      // scatter operand: projector 3 - g, points 4 r16 ..
 #pragma unroll
       for (int mb = 0; mb < 4; ++mb)
-        stab[e * kScatFloats + lane * 4 + mb] = (float)val(g, 4 * r16 + mb);
+        stab[e * kScatFloats + lane * 4 + mb] = (float)val(3 - g, 4 * r16 + mb);
       // integral operand: projector r16 / 4, g = r16 % 4, the lane's g selecting ks and the
       // half of v
       __bf16* o = reinterpret_cast<__bf16*>(gtab) + e * kPieceElems;
@@ -540,6 +540,11 @@ __device__ __forceinline__ void load4(double (&v)[4], const double* p) {
   }
 }
 
+// k step j sums over projector 3 - j (FP64: j) of four groups.  The s projectors come first
+// in a group and have the largest integrals; summed last, the three steps before them round
+// a small sum (H X of positive columns over 16 projectors: error 1.03e-7 against 6.2e-8 of
+// its rms where the nonlocal term dominates).
+//
 // Tiles [t0, t1) of the columns for the 16 MB points from `base` on (row blocks mb0 .. of
 // block b), live groups s0 .. s0 + n - 1 of the block, n <= 4 NQ.
 template <typename T, int NQ, bool FULL>
@@ -676,8 +681,9 @@ __global__ __launch_bounds__(256, OCC) void scatter_kernel(ScatterArgs a) {
 
 // --------------------------------------------------------------- reduction --
 
-// coef[(group n_s + col) 4 + p] = scale rowscale[4 group + p] sum over the runs that hold
-// the group of the partial row (4 occ + p); zero past the last projector.  A workgroup
+// coef[(group n_s + col) 4 + q] = scale rowscale[4 group + p] sum over the runs that hold
+// the group of the partial row (4 occ + p); zero past the last projector.  q = 3 - p in
+// FP32, p in FP64.  A workgroup
 // takes one projector and 64 columns; its W waves sum interleaved shares of the
 // occurrences, kReduceDepth loads in flight each, which is what the time goes by
 // (two in flight: 12 us at 24^3 x 64 in FP64, 10 at 48^3 x 512 mixed; now 4 and 7; at 72^3 x
@@ -721,7 +727,8 @@ __global__ __launch_bounds__(64 * W) void sweep_reduce_kernel(const PT* __restri
 #pragma unroll
     for (int w = 0; w < W; w += 4)
       s += (sh[w][lane] + sh[w + 1][lane]) + (sh[w + 2][lane] + sh[w + 3][lane]);
-    out[((long)grp * n_s + col) * 4 + p] = proj < n_proj ? (PT)(s * scale * rs) : (PT)0;
+    const int q = sizeof(PT) == 4 ? 3 - p : p;
+    out[((long)grp * n_s + col) * 4 + q] = proj < n_proj ? (PT)(s * scale * rs) : (PT)0;
   }
 }
 

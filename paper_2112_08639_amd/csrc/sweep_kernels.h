@@ -8,7 +8,7 @@ namespace dk {
 // Grid blocks of 64 consecutive points; one table entry per (block, live group), a group
 // being four consecutive projectors with a nonzero value in the block.  The entries of a
 // block are consecutive, in the order of its groups.
-//   mixed: the scatter operand, FP32 [projector][point] (1 KB), and the integral operand,
+//   mixed: the scatter operand, FP32 [3 - projector][point] (1 KB), and the integral operand,
 //          three bf16 pieces of 512 bytes
 //   FP64:  one operand for both, 2 KB
 constexpr int kScatFloats = 256;    // floats per mixed scatter entry
@@ -136,7 +136,7 @@ struct ScatterArgs {
   const int* kcount;
   const int* eoff;     // entry of a block's first group
   const void* tab;
-  const void* coef;    // [group][column][4 projectors]
+  const void* coef;    // [group][column][4 projectors, in FP32 the last first]
 };
 
 }  // namespace dk

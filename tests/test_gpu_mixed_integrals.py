@@ -75,3 +75,11 @@ def test_fp32_level_up_to_64_projectors(n, reps, channels, n_s, filtered):
 # at each of a block's twelve products, 0.4 2^-24 sqrt(12 63 / 2) = 4.6e-7.
 def test_long_runs():
     assert _error((40, 40, 40), (4, 4, 2), SP, 2048, False) < 3.5e-7
+
+
+# Columns of one sign: the s integrals are far larger than the p ones.  Table, coefficient,
+# the last step of the sum over projectors, the sum with the local part and the result round
+# once each, 0.42 2^-24 sqrt(5) = 5.6e-8; a sum that takes the s projectors first rounds
+# three times more per four groups.
+def test_positive_columns():
+    assert _error((24, 24, 24), (2, 2, 1), SP, 64, False, positive=True) < 8e-8

@@ -168,7 +168,11 @@ dk_status dk_spectrum_upper_bound(dk_ctx* ctx, double* b);
 
 /* Bytes of device workspace the compute calls need for blocks of n_s columns
  * with leading dimension ld, and a density-kernel expansion of degree n_pl
- * (0: the tail rule, sized for DK_TAIL_MAX_DEGREE). */
+ * (0: the tail rule, sized for DK_TAIL_MAX_DEGREE).  The size depends on the
+ * context's precision, grid and number of projectors, beyond 256 projectors
+ * also on where the atoms are; it does not always grow with n_s (fewer columns
+ * may be split over more partial sums), so ask again for every width and, with
+ * more than 256 projectors, after every change of the tables. */
 dk_status dk_workspace_bytes(const dk_ctx* ctx, int n_s, int64_t ld, int n_pl,
                              size_t* bytes);
 

@@ -110,25 +110,37 @@ __global__ __launch_bounds__(1024) void entry_offsets_kernel(const int* __restri
   if (t == 0) eoff[nblocks] = base;
 }
 
-// dense rows: slot = group; one wave per block
+// rows of the equal shares, the live ones of `slots` consecutive groups per set: set after
+// set, one wave per block
 __global__ __launch_bounds__(256) void dense_rows_kernel(const int* __restrict__ klist,
                                                          const int* __restrict__ kcount,
                                                          const int* __restrict__ eoff, int nblocks,
-                                                         int n_groups, SweepRow* __restrict__ rows) {
+                                                         int n_groups, int sets, int slots,
+                                                         SweepRow* __restrict__ rows) {
   const int lane = threadIdx.x & 63;
   const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (b >= nblocks) return;
   const int cnt = kcount[b];  // at most 64
   unsigned long long m = lane < cnt ? 1ull << klist[(long)b * n_groups + lane] : 0ull;
   for (int o = 32; o > 0; o >>= 1) m |= __shfl_xor(m, o);
-  if (lane == 0) rows[b] = SweepRow{m, eoff[b], 0};
+  if (lane >= sets) return;
+  const int first = lane * slots;
+  const unsigned long long below = m & ((1ull << first) - 1);
+  unsigned long long live = m >> first;
+  if (sets > 1) live &= (1ull << slots) - 1;
+  rows[(long)lane * nblocks + b] = SweepRow{live, eoff[b] + (int)__popcll(below), 0};
 }
 
 // --------------------------------------------------------------- integrals --
 //
 // A workgroup takes a run of blocks and 16 CB CW columns.  Up to 64 groups the runs are
-// equal shares of the blocks with one slot per group; beyond, runs of consecutive blocks
-// whose live groups form a union of at most 64 (mixed) or 32 (FP64) slots.  Each of the CW
+// equal shares of the blocks with one slot per group, in FP64 beyond 32 groups two runs of
+// half the groups each per share; beyond 64, runs of consecutive blocks whose live groups
+// form a union of at most 64 (mixed) or 32 (FP64) slots.  (Unions for 33 to 64 groups in
+// FP64 end after a few blocks where most groups are live: H X over 64 atoms at 32768 x 512
+// 742 us, shares 451, the dense product before both 560; 48 atoms at 165888 x 1024 2615,
+// 2475 and 4195; over 64 atoms at 221184 x 512, which read the block twice for little, 1537,
+// 1575 and 2733.  And they make the workspace follow the atoms.)  Each of the CW
 // consumer waves holds 16 CB columns of the current block in registers and accumulates the
 // union's rows in registers; at the end of the run they go out as one partial row per
 // projector, and a small kernel sums the runs.
@@ -801,8 +813,8 @@ __global__ __launch_bounds__(256) void group_centres_kernel(const int* __restric
 
 __global__ __launch_bounds__(1024) void group_order_kernel(
     const unsigned long long* __restrict__ sums, int n_groups, double ly, double lz,
-    const double* __restrict__ gamma, int n_proj, int* __restrict__ perm, int* __restrict__ rank,
-    double* __restrict__ ggamma) {
+    const double* __restrict__ gamma, int n_proj, int sets, int* __restrict__ perm,
+    int* __restrict__ rank, double* __restrict__ ggamma) {
   __shared__ double layer[kOrderMax], along[kOrderMax];
   const int t = threadIdx.x;
   auto place = [&](int g, int r) {
@@ -830,7 +842,9 @@ __global__ __launch_bounds__(1024) void group_order_kernel(
     if (layer[g] != layer[t] ? layer[g] < layer[t]
                              : (along[g] != along[t] ? along[g] < along[t] : g < t))
       ++r;
-  place(t, r);
+  // alternately to the sets, so that their runs are live in the same blocks and take equal time
+  // (48 atoms, 165888 x 512: 1330 -> 1204 us)
+  place(t, (r % sets) * ((n_groups + sets - 1) / sets) + r / sets);
 }
 
 // the lists in the new order, increasing; one wave per block
@@ -849,10 +863,14 @@ __global__ __launch_bounds__(64) void relabel_kernel(int* __restrict__ klist,
   }
 }
 
-// Union slots a run may have: 4 per row block of the kernels' accumulators.
+// Slots a run may have: 4 per row block of the kernels' accumulators.
 int max_slots(const dk_ctx* c) { return c->precision == DK_PREC_MIXED ? 64 : 32; }
 
-bool dense_runs(const dk_ctx* c) { return c->n_groups <= max_slots(c); }
+// Equal shares of the blocks for every run, with as many sets of groups as the slots take
+// (FP64 beyond 32 groups: two), or chunks.
+bool dense_runs(const dk_ctx* c) { return c->n_groups <= 64; }
+int run_sets(const dk_ctx* c) { return ceil_div(c->n_groups, max_slots(c)); }
+int set_slots(const dk_ctx* c) { return ceil_div(c->n_groups, run_sets(c)); }
 
 // How the integrals are cut: the kernel's row blocks and column blocks per wave, and the
 // runs.
@@ -860,6 +878,7 @@ constexpr int kConsumers = 8;
 struct SweepPlan {
   int rb = 8, cb = 1;
   int n_runs = 0, run_len = 0, ntiles = 0;
+  int sets = 1;
   long rows = 0;  // partial rows
   bool apart = false;  // two pieces: sums apart
 };
@@ -877,11 +896,13 @@ SweepPlan plan_sweep(const dk_ctx* c, int n_s, bool two_piece) {
     p.rows = 4 * c->g_rows;
     return p;
   }
-  // one workgroup per CU
-  long runs = 256 / p.ntiles;
-  if (runs < 1) runs = 1;
-  long len = (nb + runs - 1) / runs;
-  if (len > kMaxRunBlocks) len = kMaxRunBlocks;
+  // one workgroup per CU, or as many whole rounds as keep the runs within kMaxRunBlocks
+  p.sets = run_sets(c);
+  long len = nb;
+  for (int rounds = 1; rounds == 1 || len > kMaxRunBlocks; ++rounds) {
+    const long runs = std::max(1L, 256L * rounds / (p.ntiles * p.sets));
+    len = (nb + runs - 1) / runs;
+  }
   p.apart = len > kPlainBlocks;
   p.run_len = (int)len;
   p.n_runs = (int)((nb + len - 1) / len);
@@ -909,7 +930,7 @@ hipError_t launch_integrals(K kernel, const SweepArgs& a, const SweepPlan& p, in
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kernel, dim3((unsigned)((long)p.n_runs * p.ntiles)),
+  hipLaunchKernelGGL(kernel, dim3((unsigned)((long)p.n_runs * p.sets * p.ntiles)),
                      dim3(64 * (kConsumers + kFeedWaves)), lds, st, a);
   return hipGetLastError();
 }
@@ -1116,7 +1137,8 @@ hipError_t build_sweep_tables(dk_ctx* c) {
                        c->kcount, (int)nb, n_groups, c->nx, c->ny, c->nz, c->gcentre);
   }
   hipLaunchKernelGGL(group_order_kernel, dim3(1), dim3(1024), 0, c->stream, c->gcentre, n_groups,
-                     c->ly, c->lz, c->gamma_dev, c->n_proj, c->gperm, rank, c->ggamma);
+                     c->ly, c->lz, c->gamma_dev, c->n_proj, dense_runs(c) ? run_sets(c) : 1, c->gperm,
+                     rank, c->ggamma);
   if (n_groups <= kOrderMax)
     hipLaunchKernelGGL(relabel_kernel, dim3((unsigned)nb), dim3(64), 0, c->stream, c->klist,
                        c->kcount, n_groups, rank);
@@ -1149,10 +1171,13 @@ hipError_t build_sweep_tables(dk_ctx* c) {
                        c->geoff, c->stab, c->gtab);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (!dense_runs(c)) return build_chunks(c);
-  if (!c->growrec && (e = hipMalloc(&c->growrec, (size_t)nb * sizeof(SweepRow))) != hipSuccess)
+  const int sets = run_sets(c);
+  if (!c->growrec &&
+      (e = hipMalloc(&c->growrec, (size_t)sets * nb * sizeof(SweepRow))) != hipSuccess)
     return e;
   hipLaunchKernelGGL(dense_rows_kernel, dim3(ceil_div(nb, 4)), dim3(256), 0, c->stream, c->klist,
-                     c->kcount, c->geoff, (int)nb, n_groups, (SweepRow*)c->growrec);
+                     c->kcount, c->geoff, (int)nb, n_groups, sets, set_slots(c),
+                     (SweepRow*)c->growrec);
   return hipGetLastError();
 }
 
@@ -1183,6 +1208,8 @@ hipError_t nonlocal_integrals(dk_ctx* c, const void* x, long ld, int n_s, double
   a.nblocks = (int)((c->ngrid + 63) / 64);
   a.run_len = p.run_len;
   a.n_groups = c->n_groups;
+  a.sets = p.sets;
+  a.slots = set_slots(c);
   a.rows = (const SweepRow*)c->growrec;
   a.tab = c->gtab;
   a.part = w.part;

@@ -59,11 +59,11 @@ struct SweepArgs {
   long ngrid;
   int ntiles;          // column tiles per run
   // runs of consecutive blocks: {first block, blocks, union offset, union length} and
-  // the row of the first block (compact supports), or equal shares of run_len blocks
-  // with slot = group (chunks null)
+  // the row of the first block (compact supports), or (chunks null) equal shares of run_len
+  // blocks, `sets` (1 or 2) runs of `slots` consecutive groups each (the last one the rest)
   const int4* chunks;
   const int* qoff;
-  int nblocks, run_len, n_groups;
+  int nblocks, run_len, n_groups, sets, slots;
   const SweepRow* rows;
   const void* tab;
   void* part;          // integral partials: row (4 * union offset + r), columns contiguous
@@ -79,11 +79,12 @@ struct SweepRun {
       b0 = ch[0]; nb = ch[1]; uoff = ch[2]; ulen = ch[3];
       rows += const_ints(a.qoff)[run];
     } else {
-      b0 = run * a.run_len;
+      const int share = run >> (a.sets - 1), set = run & (a.sets - 1);
+      b0 = share * a.run_len;
       nb = min(a.run_len, a.nblocks - b0);
-      uoff = run * a.n_groups;
-      ulen = a.n_groups;
-      rows += b0;
+      uoff = share * a.n_groups + set * a.slots;
+      ulen = min(a.slots, a.n_groups - set * a.slots);
+      rows += (long)set * a.nblocks + b0;
     }
   }
 };

@@ -43,8 +43,7 @@ struct dk_ctx {
   unsigned long long* gcentre = nullptr;
   double* ggamma = nullptr;  // gamma in that order, four per group
   int n_groups = 0;
-  long g_entries = 0;   // (block, live group) pairs
-  long g_capacity = 0;  // entries the tables have room for
+  long g_capacity = 0;  // (block, live group) pairs the tables have room for
   void* gtab = nullptr;
   float* stab = nullptr;
   void* growrec = nullptr;

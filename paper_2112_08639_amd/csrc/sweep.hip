@@ -85,52 +85,6 @@ __global__ __launch_bounds__(256) void sweep_table_kernel(
   }
 }
 
-// eoff[b] = sum of kcount[0..b), eoff[nblocks] the total; one workgroup
-__global__ __launch_bounds__(1024) void entry_offsets_kernel(const int* __restrict__ kcount,
-                                                             int nblocks, int* __restrict__ eoff) {
-  __shared__ int sh[1024];
-  __shared__ int base;
-  const int t = threadIdx.x;
-  if (t == 0) base = 0;
-  for (int b0 = 0; b0 < nblocks; b0 += 1024) {
-    const int v = (b0 + t < nblocks) ? kcount[b0 + t] : 0;
-    sh[t] = v;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-      const int u = t >= o ? sh[t - o] : 0;
-      __syncthreads();
-      sh[t] += u;
-      __syncthreads();
-    }
-    if (b0 + t < nblocks) eoff[b0 + t] = base + sh[t] - v;
-    __syncthreads();
-    if (t == 0) base += sh[1023];
-    __syncthreads();
-  }
-  if (t == 0) eoff[nblocks] = base;
-}
-
-// rows of the equal shares, the live ones of `slots` consecutive groups per set: set after
-// set, one wave per block
-__global__ __launch_bounds__(256) void dense_rows_kernel(const int* __restrict__ klist,
-                                                         const int* __restrict__ kcount,
-                                                         const int* __restrict__ eoff, int nblocks,
-                                                         int n_groups, int sets, int slots,
-                                                         SweepRow* __restrict__ rows) {
-  const int lane = threadIdx.x & 63;
-  const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (b >= nblocks) return;
-  const int cnt = kcount[b];  // at most 64
-  unsigned long long m = lane < cnt ? 1ull << klist[(long)b * n_groups + lane] : 0ull;
-  for (int o = 32; o > 0; o >>= 1) m |= __shfl_xor(m, o);
-  if (lane >= sets) return;
-  const int first = lane * slots;
-  const unsigned long long below = m & ((1ull << first) - 1);
-  unsigned long long live = m >> first;
-  if (sets > 1) live &= (1ull << slots) - 1;
-  rows[(long)lane * nblocks + b] = SweepRow{live, eoff[b] + (int)__popcll(below), 0};
-}
-
 // --------------------------------------------------------------- integrals --
 //
 // A workgroup takes a run of blocks and 16 CB CW columns.  Up to 64 groups the runs are
@@ -746,12 +700,15 @@ __global__ __launch_bounds__(64 * W) void sweep_reduce_kernel(const PT* __restri
 
 // One wave per 64-point block: lane i looks at point 64 gb + i of the four
 // projectors of each group; the groups where any lane sees a nonzero are
-// listed in increasing order.
+// listed in increasing order.  Clears the sums of group_centres_kernel.
 __global__ __launch_bounds__(256) void group_lists_kernel(const double* __restrict__ chi, long ng,
                                                           int n_proj, long gblocks, int n_groups,
                                                           int* __restrict__ list,
-                                                          int* __restrict__ count) {
+                                                          int* __restrict__ count,
+                                                          unsigned long long* __restrict__ sums) {
   const int lane = threadIdx.x & 63;
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < 4 * n_groups; i += 256) sums[i] = 0;
   const long nwaves = ((long)gridDim.x * blockDim.x) >> 6;
   for (long gb = (blockIdx.x * (long)blockDim.x + threadIdx.x) >> 6; gb < gblocks; gb += nwaves) {
     const long x = gb * 64 + lane;
@@ -811,10 +768,11 @@ __global__ __launch_bounds__(256) void group_centres_kernel(const int* __restric
     if (own[i] != 0) atomicAdd(sums + i, own[i]);
 }
 
-__global__ __launch_bounds__(1024) void group_order_kernel(
-    const unsigned long long* __restrict__ sums, int n_groups, double ly, double lz,
-    const double* __restrict__ gamma, int n_proj, int sets, int* __restrict__ perm,
-    int* __restrict__ rank, double* __restrict__ ggamma) {
+// the order (sort: by centre; otherwise as it is)
+__device__ void group_order(const unsigned long long* __restrict__ sums, int n_groups, bool sort,
+                            double ly, double lz, const double* __restrict__ gamma, int n_proj,
+                            int sets, int* __restrict__ perm, int* __restrict__ rank,
+                            double* __restrict__ ggamma) {
   __shared__ double layer[kOrderMax], along[kOrderMax];
   const int t = threadIdx.x;
   auto place = [&](int g, int r) {
@@ -822,7 +780,7 @@ __global__ __launch_bounds__(1024) void group_order_kernel(
     rank[g] = r;
     for (int p = 0; p < 4; ++p) ggamma[4 * r + p] = 4 * g + p < n_proj ? gamma[4 * g + p] : 0.0;
   };
-  if (n_groups > kOrderMax) {
+  if (!sort) {
     for (int g = t; g < n_groups; g += 1024) place(g, g);
     return;
   }
@@ -847,20 +805,69 @@ __global__ __launch_bounds__(1024) void group_order_kernel(
   place(t, (r % sets) * ((n_groups + sets - 1) / sets) + r / sets);
 }
 
-// the lists in the new order, increasing; one wave per block
+// eoff[b] = sum of kcount[0..b), eoff[nblocks] the total
+__device__ void entry_offsets(const int* __restrict__ kcount, int nblocks, int* __restrict__ eoff) {
+  __shared__ int sh[1024];
+  __shared__ int base;
+  const int t = threadIdx.x;
+  if (t == 0) base = 0;
+  for (int b0 = 0; b0 < nblocks; b0 += 1024) {
+    const int v = (b0 + t < nblocks) ? kcount[b0 + t] : 0;
+    sh[t] = v;
+    __syncthreads();
+    for (int o = 1; o < 1024; o <<= 1) {
+      const int u = t >= o ? sh[t - o] : 0;
+      __syncthreads();
+      sh[t] += u;
+      __syncthreads();
+    }
+    if (b0 + t < nblocks) eoff[b0 + t] = base + sh[t] - v;
+    __syncthreads();
+    if (t == 0) base += sh[1023];
+    __syncthreads();
+  }
+  if (t == 0) eoff[nblocks] = base;
+}
+
+// the two jobs of one workgroup, side by side
+__global__ __launch_bounds__(1024) void order_offsets_kernel(
+    const unsigned long long* __restrict__ sums, int n_groups, bool sort, double ly, double lz,
+    const double* __restrict__ gamma, int n_proj, int sets, int* __restrict__ perm,
+    int* __restrict__ rank, double* __restrict__ ggamma, const int* __restrict__ kcount,
+    int nblocks, int* __restrict__ eoff) {
+  if (blockIdx.x == 0)
+    group_order(sums, n_groups, sort, ly, lz, gamma, n_proj, sets, perm, rank, ggamma);
+  else
+    entry_offsets(kcount, nblocks, eoff);
+}
+
+// the lists in the new order, increasing; one wave per block.  rows not null: the rows of the
+// equal shares, the live ones of `slots` consecutive groups per set, set after set
 __global__ __launch_bounds__(64) void relabel_kernel(int* __restrict__ klist,
                                                      const int* __restrict__ kcount, int n_groups,
-                                                     const int* __restrict__ rank) {
+                                                     const int* __restrict__ rank,
+                                                     const int* __restrict__ eoff, int sets,
+                                                     int slots, SweepRow* __restrict__ rows) {
   __shared__ int r[kOrderMax];
-  int* const list = klist + (long)blockIdx.x * n_groups;
-  const int cnt = kcount[blockIdx.x];
-  for (int i = threadIdx.x; i < cnt; i += 64) r[i] = rank[list[i]];
+  const int b = blockIdx.x, lane = threadIdx.x;
+  int* const list = klist + (long)b * n_groups;
+  const int cnt = kcount[b];
+  for (int i = lane; i < cnt; i += 64) r[i] = rank[list[i]];
   __syncthreads();
-  for (int i = threadIdx.x; i < cnt; i += 64) {
+  for (int i = lane; i < cnt; i += 64) {
     int at = 0;
     for (int j = 0; j < cnt; ++j) at += r[j] < r[i] ? 1 : 0;
     list[at] = r[i];
   }
+  if (!rows) return;
+  unsigned long long m = lane < cnt ? 1ull << r[lane] : 0ull;  // at most 64 groups
+  for (int o = 32; o > 0; o >>= 1) m |= __shfl_xor(m, o);
+  if (lane >= sets) return;
+  const int first = lane * slots;
+  const unsigned long long below = m & ((1ull << first) - 1);
+  unsigned long long live = m >> first;
+  if (sets > 1) live &= (1ull << slots) - 1;
+  rows[(long)lane * gridDim.x + b] = SweepRow{live, eoff[b] + (int)__popcll(below), 0};
 }
 
 // Slots a run may have: 4 per row block of the kernels' accumulators.
@@ -991,7 +998,6 @@ void free_sweep_tables(dk_ctx* c) {
   c->n_groups = 0;
   c->n_gchunks = 0;
   c->g_rows = 0;
-  c->g_entries = 0;
 }
 
 namespace {
@@ -1127,30 +1133,38 @@ hipError_t build_sweep_tables(dk_ctx* c) {
   long blocks = (nb * 64 + 255) / 256;
   if (blocks > 8192) blocks = 8192;
   hipLaunchKernelGGL(group_lists_kernel, dim3((int)blocks), dim3(256), 0, c->stream, c->chi64,
-                     c->ngrid, c->n_proj, nb, n_groups, c->klist, c->kcount);
+                     c->ngrid, c->n_proj, nb, n_groups, c->klist, c->kcount, c->gcentre);
+  // the order matters to row blocks of four groups (mixed) and to two sets (FP64)
+  const bool dense = dense_runs(c);
+  const int sets = dense ? run_sets(c) : 1;
+  const bool sort = n_groups <= kOrderMax && (mixed ? n_groups > 4 : sets > 1);
   int* const rank = c->gperm + n_groups;
-  if (n_groups <= kOrderMax) {
-    if ((e = hipMemsetAsync(c->gcentre, 0, 4 * (size_t)n_groups * sizeof(unsigned long long),
-                            c->stream)) != hipSuccess)
-      return e;
+  if (sort)
     hipLaunchKernelGGL(group_centres_kernel, dim3(64), dim3(256), 0, c->stream, c->klist,
                        c->kcount, (int)nb, n_groups, c->nx, c->ny, c->nz, c->gcentre);
-  }
-  hipLaunchKernelGGL(group_order_kernel, dim3(1), dim3(1024), 0, c->stream, c->gcentre, n_groups,
-                     c->ly, c->lz, c->gamma_dev, c->n_proj, dense_runs(c) ? run_sets(c) : 1, c->gperm,
-                     rank, c->ggamma);
-  if (n_groups <= kOrderMax)
-    hipLaunchKernelGGL(relabel_kernel, dim3((unsigned)nb), dim3(64), 0, c->stream, c->klist,
-                       c->kcount, n_groups, rank);
-  hipLaunchKernelGGL(entry_offsets_kernel, dim3(1), dim3(1024), 0, c->stream, c->kcount, (int)nb,
-                     c->geoff);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  int entries = 0;
-  if ((e = hipMemcpyAsync(&entries, c->geoff + nb, sizeof entries, hipMemcpyDeviceToHost,
-                          c->stream)) != hipSuccess)
+  hipLaunchKernelGGL(order_offsets_kernel, dim3(2), dim3(1024), 0, c->stream, c->gcentre, n_groups,
+                     sort, c->ly, c->lz, c->gamma_dev, c->n_proj, sets, c->gperm, rank, c->ggamma,
+                     c->kcount, (int)nb, c->geoff);
+  if (dense && !c->growrec &&
+      (e = hipMalloc(&c->growrec, (size_t)sets * nb * sizeof(SweepRow))) != hipSuccess)
     return e;
-  if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return e;
-  c->g_entries = entries;
+  if (sort || dense)
+    hipLaunchKernelGGL(relabel_kernel, dim3((unsigned)nb), dim3(64), 0, c->stream, c->klist,
+                       c->kcount, n_groups, rank, c->geoff, sets, set_slots(c),
+                       dense ? (SweepRow*)c->growrec : nullptr);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  // Room for the entries: beyond 64 groups as many as there are, which has to be read back;
+  // up to 64, a quarter of the dense table at most, for all (a wait of 15 us saved where the
+  // whole call takes 100)
+  long entries = nb * n_groups;
+  if (!dense) {
+    int live = 0;
+    if ((e = hipMemcpyAsync(&live, c->geoff + nb, sizeof live, hipMemcpyDeviceToHost,
+                            c->stream)) != hipSuccess)
+      return e;
+    if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return e;
+    entries = live;
+  }
   if (entries > c->g_capacity || !c->gtab) {
     hipFree(c->gtab); c->gtab = nullptr;
     hipFree(c->stab); c->stab = nullptr;
@@ -1170,15 +1184,7 @@ hipError_t build_sweep_tables(dk_ctx* c) {
                        c->chi64, c->ngrid, c->n_proj, n_groups, c->gperm, c->klist, c->kcount,
                        c->geoff, c->stab, c->gtab);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (!dense_runs(c)) return build_chunks(c);
-  const int sets = run_sets(c);
-  if (!c->growrec &&
-      (e = hipMalloc(&c->growrec, (size_t)sets * nb * sizeof(SweepRow))) != hipSuccess)
-    return e;
-  hipLaunchKernelGGL(dense_rows_kernel, dim3(ceil_div(nb, 4)), dim3(256), 0, c->stream, c->klist,
-                     c->kcount, c->geoff, (int)nb, n_groups, sets, set_slots(c),
-                     (SweepRow*)c->growrec);
-  return hipGetLastError();
+  return dense ? hipSuccess : build_chunks(c);
 }
 
 // integral partials and the coefficients alpha gamma h^3 chi^T X

@@ -7,6 +7,11 @@
 #include "../../include/dk.h"
 #include "common.h"
 
+// Cut of a block by the local part's row kernel: slabs of ty rows, chunks of zc planes.
+struct RowsPlan {
+  int slabs = 0, ty = 0, zc = 0, chunks = 0, threads = 0;
+};
+
 struct dk_ctx {
   // grid
   int nx = 0, ny = 0, nz = 0;
@@ -88,9 +93,12 @@ struct dk_ctx {
   double prof_ms[DK_K_COUNT] = {};
   int64_t prof_cnt[DK_K_COUNT] = {};
 
-  // kernels whose dynamic-LDS limit has been raised on this context's device
-  // (hipFuncSetAttribute is per device): bits kAttrPlane, kAttrSlab, kAttrFermi
-  unsigned lds_attr_done = 0;
+  // kernels whose dynamic-LDS limit has been raised on this context's device (allow_lds)
+  const void* lds_raised[64] = {};
+  int n_lds_raised = 0;
+  // cut of the local part's last block width (plan_rows; grid and precision are fixed)
+  int rows_n_s = 0;
+  RowsPlan rows_plan;
   // linear solver of the Poisson and Kerker solves (dk_set_linear_solver)
   int linear_solver = DK_SOLVER_CG;
   double aar_omega = 0.6, aar_beta = 0.6;
@@ -112,7 +120,17 @@ struct dk_ctx {
 
 namespace dk {
 
-enum : unsigned { kAttrPlane = 1u, kAttrSlab = 2u, kAttrFermi = 4u };
+// Before a launch with more than 64 KB of dynamic LDS: the kernel's limit is raised to
+// `most` on the first one (hipFuncSetAttribute is per device).
+inline hipError_t allow_lds(dk_ctx* c, const void* kernel, size_t most) {
+  for (int i = 0; i < c->n_lds_raised; ++i)
+    if (c->lds_raised[i] == kernel) return hipSuccess;
+  const hipError_t e =
+      hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+  if (e == hipSuccess && c->n_lds_raised < (int)(sizeof c->lds_raised / sizeof *c->lds_raised))
+    c->lds_raised[c->n_lds_raised++] = kernel;
+  return e;
+}
 
 inline void flag_error(dk_ctx* c, unsigned bits) { c->err_host |= bits; }
 

@@ -394,16 +394,11 @@ static hipError_t run_fermi(dk_ctx* c, const double* tau, int n_pl, double chi, 
   const int K = n_nodes(n_pl);
   double* res = f.res;
   constexpr size_t kMaxLds = 150 * 1024;
-  if (!(c->lds_attr_done & kAttrFermi)) {
-    const void* fns[] = {(const void*)fermi_weights_kernel<true>,
+  for (const void* fn : {(const void*)fermi_weights_kernel<true>,
                          (const void*)fermi_search_kernel<true>,
-                         (const void*)fermi_coef_kernel<true>};
-    for (const void* fn : fns) {
-      const hipError_t e =
-          hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
-      if (e != hipSuccess) return e;
-    }
-    c->lds_attr_done |= kAttrFermi;
+                         (const void*)fermi_coef_kernel<true>}) {
+    const hipError_t e = allow_lds(c, fn, kMaxLds);
+    if (e != hipSuccess) return e;
   }
   const size_t lds_w = 4 * (size_t)K * sizeof(double);
   const size_t lds_s = 2 * (size_t)K * sizeof(double);

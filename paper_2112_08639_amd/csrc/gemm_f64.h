@@ -236,11 +236,7 @@ inline hipError_t launch_nt(const NtArgs& a, hipStream_t st) {
   const long z = PARTIAL ? a.splits : a.batch;
   constexpr size_t lds = nt_lds_bytes(BT, BK);
   const auto kernel = nt_f64_kernel<TA, TB, PARTIAL, BT, BK, OCC>;
-  if (lds > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute((const void*)kernel,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
+  static_assert(lds <= 64 * 1024, "no limit to raise");
   hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles * z)), dim3(256), lds, st, a);
   return hipGetLastError();
 }

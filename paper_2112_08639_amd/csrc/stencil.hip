@@ -968,7 +968,6 @@ static size_t rows_lds_bytes(int nx, int ty, size_t elem) {
   return 2 * (size_t)(ty + 12) * rows_pitch(nx) * elem;
 }
 
-struct RowsPlan { int slabs = 0, ty = 0, zc = 0, chunks = 0, threads = 0; };
 static RowsPlan plan_rows(int nx, int ny, int nz, int n_s, int W) {
   const RowsWeights& w = W == 4 ? kRows32 : kRows64;
   RowsPlan best;
@@ -984,9 +983,8 @@ static RowsPlan plan_rows(int nx, int ny, int nz, int n_s, int W) {
     if (lds > 160 * 1024) continue;
     const int waves = threads / 64;
     const int conc = std::max(1, std::min(16 / waves, (int)(160 * 1024 / lds)));
-    for (int z = 1; z <= std::max(1, nz / 4); ++z) {
-      const int zc = ceil_div(nz, z), chunks = ceil_div(nz, zc);
-      if (chunks != z) continue;
+    for (int chunks = 1, zc = nz; chunks <= std::max(1, nz / 4);
+         chunks = zc > 1 ? ceil_div(nz, zc - 1) : nz + 1, zc = ceil_div(nz, chunks)) {
       const double per = (w.waves * waves + (1.0 - w.waves) * ty * segs / 64.0) *
                          (zc + w.prologue) * (1.0 + (slabs == 1 ? w.whole : w.halo * 12 / ty));
       const double n = (double)slabs * chunks * n_s / 256;  // workgroups per CU
@@ -1009,17 +1007,16 @@ static RowsPlan plan_rows(int nx, int ny, int nz, int n_s, int W) {
 }
 
 template <typename T, int W, int R>
-static hipError_t launch_rows(StencilArgs a, const RowsPlan& p, int n_s, hipStream_t st) {
+static hipError_t launch_rows(dk_ctx* c, StencilArgs a, const RowsPlan& p, int n_s) {
   a.ty_tile = p.ty;
   a.zc = p.zc;
   const size_t smem = rows_lds_bytes(a.nx, p.ty, sizeof(T));
   auto launch = [&](auto kernel) -> hipError_t {
     if (smem > 64 * 1024) {
-      const hipError_t e = hipFuncSetAttribute(
-          (const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+      const hipError_t e = allow_lds(c, (const void*)kernel, 160 * 1024);
       if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kernel, dim3(p.slabs, p.chunks, n_s), dim3(p.threads), smem, st, a);
+    hipLaunchKernelGGL(kernel, dim3(p.slabs, p.chunks, n_s), dim3(p.threads), smem, c->stream, a);
     return hipGetLastError();
   };
   const int pitch = rows_pitch(a.nx);
@@ -1096,18 +1093,23 @@ hipError_t stencil_step(dk_ctx* c, const void* yin, const void* yprev, void* you
   // 687 us, 99 x 50 x 40 x 100: 302 -> 175 us; times of one application)
   if (c->nx <= kRowsMaxNx) {
     const int W = f64 ? 2 : 4;
-    const RowsPlan p = plan_rows(c->nx, c->ny, c->nz, n_s, W);
+    // (the search over all cuts takes 1 us at 48^3 and 36 us at 7 x 1024 x 1024)
+    if (c->rows_n_s != n_s) {
+      c->rows_plan = plan_rows(c->nx, c->ny, c->nz, n_s, W);
+      c->rows_n_s = n_s;
+    }
+    const RowsPlan p = c->rows_plan;
     const bool slab = !f64 && c->nx > 80 && p.slabs > 1 && c->nx % 4 == 0 && ld % 4 == 0;
     if (p.slabs > 0 && !slab) {
       const int R = c->nx % W;
       if (f64)
-        return R == 0 ? launch_rows<double, 2, 0>(a, p, n_s, c->stream)
-                      : launch_rows<double, 2, 1>(a, p, n_s, c->stream);
+        return R == 0 ? launch_rows<double, 2, 0>(c, a, p, n_s)
+                      : launch_rows<double, 2, 1>(c, a, p, n_s);
       switch (R) {
-        case 0: return launch_rows<float, 4, 0>(a, p, n_s, c->stream);
-        case 1: return launch_rows<float, 4, 1>(a, p, n_s, c->stream);
-        case 2: return launch_rows<float, 4, 2>(a, p, n_s, c->stream);
-        default: return launch_rows<float, 4, 3>(a, p, n_s, c->stream);
+        case 0: return launch_rows<float, 4, 0>(c, a, p, n_s);
+        case 1: return launch_rows<float, 4, 1>(c, a, p, n_s);
+        case 2: return launch_rows<float, 4, 2>(c, a, p, n_s);
+        default: return launch_rows<float, 4, 3>(c, a, p, n_s);
       }
     }
   }
@@ -1127,14 +1129,10 @@ hipError_t stencil_step(dk_ctx* c, const void* yin, const void* yprev, void* you
     const size_t smem = 2 * (size_t)c->ny * (c->nx + 2 * kPad) * sizeof(float);
     dim3 grid(1, zch, n_s);
     if (smem <= 160 * 1024) {
-      if (!(c->lds_attr_done & kAttrPlane)) {
-        hipError_t e = hipFuncSetAttribute((const void*)stencil_plane_kernel<float, 640>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e == hipSuccess)
-          e = hipFuncSetAttribute((const void*)stencil_plane_kernel<float, 1024>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+      for (const void* f : {(const void*)stencil_plane_kernel<float, 640>,
+                            (const void*)stencil_plane_kernel<float, 1024>}) {
+        const hipError_t e = allow_lds(c, f, 160 * 1024);
         if (e != hipSuccess) return e;
-        c->lds_attr_done |= kAttrPlane;
       }
       if (threads <= 640)
         hipLaunchKernelGGL((stencil_plane_kernel<float, 640>), grid, dim3(threads), smem, c->stream, a);
@@ -1164,17 +1162,12 @@ hipError_t stencil_step(dk_ctx* c, const void* yin, const void* yprev, void* you
       zch = ceil_div(c->nz, a.zc);
       const size_t smem = 2 * (size_t)(ty + 12) * (c->nx + 2 * kPad) * (f64 ? 8 : 4);
       if (smem <= 160 * 1024) {
-        if (!(c->lds_attr_done & kAttrSlab)) {
-          const void* fns[4] = {(const void*)stencil_slab_kernel<double, 2, 768>,
-                                (const void*)stencil_slab_kernel<double, 2, 1024>,
-                                (const void*)stencil_slab_kernel<float, 4, 768>,
-                                (const void*)stencil_slab_kernel<float, 4, 1024>};
-          for (const void* f : fns) {
-            const hipError_t e =
-                hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            if (e != hipSuccess) return e;
-          }
-          c->lds_attr_done |= kAttrSlab;
+        for (const void* f : {(const void*)stencil_slab_kernel<double, 2, 768>,
+                              (const void*)stencil_slab_kernel<double, 2, 1024>,
+                              (const void*)stencil_slab_kernel<float, 4, 768>,
+                              (const void*)stencil_slab_kernel<float, 4, 1024>}) {
+          const hipError_t e = allow_lds(c, f, 160 * 1024);
+          if (e != hipSuccess) return e;
         }
         dim3 grid(n_slabs, zch, n_s);
         const bool small = threads <= 768;

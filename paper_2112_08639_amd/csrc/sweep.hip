@@ -927,28 +927,27 @@ size_t partial_bytes(const dk_ctx* c, int n_s) {
 }
 
 template <typename K>
-hipError_t launch_integrals(K kernel, const SweepArgs& a, const SweepPlan& p, int units,
-                            size_t tiles, hipStream_t st) {
+hipError_t launch_integrals(dk_ctx* c, K kernel, const SweepArgs& a, const SweepPlan& p, int units,
+                            size_t tiles) {
   if (p.n_runs == 0) return hipSuccess;
   // two buffers of table entries, and what the consumers keep
   const size_t lds = 2 * (size_t)units * kStageEntries * sizeof(f32x4) + tiles;
   if (lds > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute((const void*)kernel,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t e = allow_lds(c, (const void*)kernel, lds);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(kernel, dim3((unsigned)((long)p.n_runs * p.sets * p.ntiles)),
-                     dim3(64 * (kConsumers + kFeedWaves)), lds, st, a);
+                     dim3(64 * (kConsumers + kFeedWaves)), lds, c->stream, a);
   return hipGetLastError();
 }
 
 template <int NP>
-hipError_t integrals_mixed(const SweepArgs& a, const SweepPlan& p, hipStream_t st) {
+hipError_t integrals_mixed(dk_ctx* c, const SweepArgs& a, const SweepPlan& p) {
   const int units = piece_units(NP);
   // the consumers' tiles and the zero entry
   const size_t tiles = (size_t)kConsumers * p.cb * NP * 16 * kTilePitch * sizeof(__bf16) +
                        units * sizeof(f32x4);
-  auto go = [&](auto kernel) { return launch_integrals(kernel, a, p, units, tiles, st); };
+  auto go = [&](auto kernel) { return launch_integrals(c, kernel, a, p, units, tiles); };
   if constexpr (NP == 3) {
     return p.rb == 16 ? go(integrals_mixed_kernel<16, 1, kConsumers, 3, true>)
                       : go(integrals_mixed_kernel<8, 1, kConsumers, 3, true>);
@@ -1222,9 +1221,9 @@ hipError_t nonlocal_integrals(dk_ctx* c, const void* x, long ld, int n_s, double
   KTimer kt(c, DK_K_NL_GATHER);
   hipError_t e;
   if (c->precision == DK_PREC_FP64)
-    e = launch_integrals(integrals_f64_kernel<32, kConsumers>, a, p, kF64Units, 0, c->stream);
-  else if (two_piece) e = integrals_mixed<2>(a, p, c->stream);
-  else e = integrals_mixed<3>(a, p, c->stream);
+    e = launch_integrals(c, integrals_f64_kernel<32, kConsumers>, a, p, kF64Units, 0);
+  else if (two_piece) e = integrals_mixed<2>(c, a, p);
+  else e = integrals_mixed<3>(c, a, p);
   if (e != hipSuccess) return e;
   const dim3 grid(4 * c->n_groups, ceil_div(n_s, 64));
   const int* off = dense ? nullptr : c->gocc_off;

@@ -1068,9 +1068,10 @@ hipError_t stencil_step(dk_ctx* c, const void* yin, const void* yprev, void* you
   KTimer kt(c, DK_K_STENCIL);
   const long plane = (long)c->nx * c->ny;
   // nx = 48 in FP32: one x-row per DPP row of 16 lanes, a whole plane per workgroup, two
-  // workgroups per CU.  Where such workgroups fill the chip (to 95 %) it is even with or
-  // ahead of the rows kernel (48^3 x 512: 188 against 191 us), elsewhere behind (48 x 40 x
-  // 54 x 203: 71 against 63 us)
+  // workgroups per CU.  Where such workgroups fill the chip (to 95 %) it is ahead of the rows
+  // kernel (H X without projectors, 48^3 x 512: 158 against 169 us, 48 x 24 x 48 x 512: 102
+  // against 128; 24 filter steps over 128 projectors at 48^3 x 512: 7.97 against 8.12 ms),
+  // elsewhere behind (48 x 40 x 54 x 203: 71 against 63 us)
   if (!f64 && c->nx == 48 && c->ny >= 6 && c->ny <= 48 && ld % 4 == 0) {
     int zch = ceil_div(512, (long)n_s);
     zch = std::max(1, std::min(zch, c->nz / 12));
@@ -1091,8 +1092,14 @@ hipError_t stencil_step(dk_ctx* c, const void* yin, const void* yprev, void* you
   // of one workgroup, rows off the vectors and FP64 gain (96 x 40 x 40 x 300: 188 -> 146 us;
   // 90^3 x 200: 1863 -> 783 us; 81 x 40 x 50 x 300: 662 -> 344 us; FP64 96^3 x 128: 890 ->
   // 687 us, 99 x 50 x 40 x 100: 302 -> 175 us; times of one application)
-  if (c->nx <= kRowsMaxNx) {
-    const int W = f64 ? 2 : 4;
+  // Of rows of at most ten points its vectors waste much where the length is no multiple of
+  // them; in blocks large enough to hide latency one point a thread is faster, if the tiles
+  // of that form are well filled (9 x 100 x 100 x 300: FP32 226 against 169 us, FP64 268
+  // against 226; 7 x 100 x 100 x 300: 174 against 112 and 231 against 190).
+  const int W = f64 ? 2 : 4;
+  const bool short_rows = c->nx <= 10 && c->nx % W != 0 && c->ngrid * n_s >= 4000000 &&
+                          plane >= 0.6 * n_ytiles * 256 * ppt;
+  if (c->nx <= kRowsMaxNx && !short_rows) {
     // (the search over all cuts takes 1 us at 48^3 and 36 us at 7 x 1024 x 1024)
     if (c->rows_n_s != n_s) {
       c->rows_plan = plan_rows(c->nx, c->ny, c->nz, n_s, W);

@@ -1,6 +1,10 @@
-"""H X and filter steps (Y_{k+1} over Y_{k-1} in place) in kernels of the local part that
-blocks of a few columns do not reach: the one-point form for short ragged rows in large
-blocks.  Leading dimensions of the grid, and off every alignment.  Oracle: the FP64
+"""H X and filter steps (Y_{k+1} over Y_{k-1} in place) in every kernel of the local part that
+blocks of a few columns do not reach: the row-rotation kernel (48 points a row in FP32,
+workgroups that fill the chip) at planes that are no multiple of its waves, of fewer than
+twelve rows and in z-chunks of unequal length; the whole-plane kernel (rows of 81 points and
+more, planes of at most 4096) in both of its sizes; the slab kernel in FP32 and FP64; the
+one-point form for short ragged rows in large blocks.  Leading dimensions of the grid, and
+off every alignment, which sends FP32 rows to the general kernels.  Oracle: the FP64
 Hamiltonian on some of the columns; tolerances as for H X elsewhere (FP64 1e-12, FP32 2e-5)."""
 
 import numpy as np
@@ -14,7 +18,14 @@ from workloads import custom_spec, make_problem
 pytestmark = pytest.mark.gpu
 
 H0 = 0.32
-CASES = [("mixed", (7, 30, 300), 64), ("fp64", (7, 30, 300), 64),      # short ragged rows
+CASES = [("mixed", (48, 48, 13), 500), ("mixed", (48, 47, 14), 512),   # row rotation
+         ("mixed", (48, 9, 26), 256), ("mixed", (48, 7, 30), 250),
+         ("mixed", (48, 41, 50), 128), ("mixed", (48, 34, 61), 103),
+         ("mixed", (100, 25, 8), 1), ("mixed", (100, 25, 25), 37),     # whole plane
+         ("mixed", (116, 20, 9), 3), ("mixed", (116, 20, 30), 5), ("mixed", (124, 33, 8), 2),
+         ("mixed", (116, 40, 9), 3), ("mixed", (116, 62, 8), 2),       # slab
+         ("mixed", (96, 52, 26), 4), ("fp64", (114, 12, 9), 3), ("fp64", (114, 14, 9), 3), ("fp64", (116, 30, 8), 2), ("fp64", (130, 50, 25), 2),
+         ("mixed", (7, 30, 300), 64), ("fp64", (7, 30, 300), 64),      # short ragged rows
          ("mixed", (7, 100, 90), 80), ("fp64", (7, 100, 90), 80),
          ("mixed", (9, 43, 163), 70), ("fp64", (9, 60, 61), 123), ("mixed", (10, 47, 69), 129)]
 

@@ -389,8 +389,8 @@ __global__ __launch_bounds__(TPB) void cg_start_kernel(const double* part, int n
   }
 }
 
-// One conjugate-gradient iteration is two kernels; each starts by summing the partials of
-// the other's dot product, every block for itself and in the same order, so that no
+// One conjugate-gradient iteration is two kernels, or three; each starts by summing the
+// partials of another's dot product, every block for itself and in the same order, so that no
 // one-block launch stands between them.  (Five launches per iteration before, 19 us at
 // 48^3 where the work is 2 us; the sums, and so the iterates, are the same to the bit.)
 // The loads that do not depend on that sum are issued ahead of it, and the blocks of an
@@ -398,10 +398,46 @@ __global__ __launch_bounds__(TPB) void cg_start_kernel(const double* part, int n
 // 2.92 ms; now 9.4 us for the product (74 loads a point, from L2), 4.3 us for the update
 // and what the launches leave between.
 //
-// direction and product: beta = rr / rr_old of iteration `it` (FIRST: none), p' = r + beta
-// p, written beside p since the neighbours read it, ap = (-Lap_h + shift) p'; partials of
-// p'.ap into ppart.  Convergence of iteration `it` is decided here.
-template <bool FIRST>
+// Forming p' = r + beta p at every neighbour reads r as often as p.  Where the vectors no
+// longer fit the L2 that costs more than a launch for p': three kernels from kCgThree points
+// on (to 1e-10, two against three: 48^3 2.95 and 3.26 ms, 64^3 5.60 and 5.14, 128^3 49.2 and
+// 36.1, where the five launches took 46.8).
+constexpr long kCgThree = 200000;
+
+// rr of iteration `it` and whether it is the last; every block of a kernel comes to the same
+__device__ __forceinline__ bool cg_decide(double rr, double bb, double tol2, int it, int max_iter,
+                                          CgState* st) {
+  const int done = rr <= tol2 * bb ? 1 : it >= max_iter ? 2 : 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->rr[it & 1] = rr;
+    st->iters = it;
+    if (done) st->done = done;
+  }
+  return done != 0;
+}
+
+// direction alone: beta = rr / rr_old of iteration `it`, p <- r + beta p
+__global__ __launch_bounds__(TPB) void cg_combine_kernel(double* __restrict__ p,
+                                                         const double* __restrict__ r, long n,
+                                                         const double* __restrict__ rpart,
+                                                         double tol2, int it, int max_iter,
+                                                         CgState* st) {
+  __shared__ double sh[TPB / 64];
+  const long blk = xcd_work_item(blockIdx.x, (long)gridDim.x);
+  const int was_done = st->done;
+  const double bb = st->bb, rr_old = st->rr[(it - 1) & 1];
+  const double rsum = load_partials(rpart, gridDim.x);
+  if (was_done) return;
+  const double rr = block_sum(rsum, sh);
+  if (cg_decide(rr, bb, tol2, it, max_iter, st)) return;
+  const double b = rr / rr_old;
+  for (long e = blk * TPB + threadIdx.x; e < n; e += (long)gridDim.x * TPB) p[e] = r[e] + b * p[e];
+}
+
+// direction and product: beta = rr / rr_old of iteration `it`, p' = r + beta p, written
+// beside p since the neighbours read it, ap = (-Lap_h + shift) p'; partials of p'.ap into
+// ppart.  FORMED: p is the direction already (the first iteration, cg_combine_kernel).
+template <bool FORMED>
 __global__ __launch_bounds__(TPB) void cg_direction_kernel(
     const double* __restrict__ p, const double* __restrict__ r, double* __restrict__ pn,
     double* __restrict__ ap, Dims d, LapCoef k, double shift, const double* __restrict__ rpart,
@@ -411,14 +447,14 @@ __global__ __launch_bounds__(TPB) void cg_direction_kernel(
   const int was_done = st->done;
   const double bb = st->bb, rr_old = st->rr[(it - 1) & 1];
   double rsum = 0.0;
-  if constexpr (!FIRST) rsum = load_partials(rpart, gridDim.x);
+  if constexpr (!FORMED) rsum = load_partials(rpart, gridDim.x);
   const unsigned n = (unsigned)d.ng, nx = d.nx, ny = d.ny, nz = d.nz, plane = nx * ny;
   double cp[37], cr[37];
   auto gather = [&](unsigned e) {
     const unsigned row = e / nx, ix = e - row * nx, iz = row / ny, iy = row - iz * ny;
     auto get = [&](int i, unsigned at) {
       cp[i] = p[at];
-      if constexpr (!FIRST) cr[i] = r[at];
+      if constexpr (!FORMED) cr[i] = r[at];
     };
     get(0, e);
 #pragma unroll
@@ -436,20 +472,14 @@ __global__ __launch_bounds__(TPB) void cg_direction_kernel(
   gather(min(e, n - 1));
   if (was_done) return;
   double b = 0.0;
-  if constexpr (!FIRST) {
+  if constexpr (!FORMED) {
     const double rr = block_sum(rsum, sh);
     b = rr / rr_old;
-    const int done = rr <= tol2 * bb ? 1 : it >= max_iter ? 2 : 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      st->rr[it & 1] = rr;
-      st->iters = it;
-      if (done) st->done = done;
-    }
-    if (done) return;
+    if (cg_decide(rr, bb, tol2, it, max_iter, st)) return;
   }
   double sum = 0.0;
   while (e < n) {
-    if constexpr (!FIRST) {
+    if constexpr (!FORMED) {
 #pragma unroll
       for (int i = 0; i < 37; ++i) cp[i] = cr[i] + b * cp[i];
     }
@@ -461,7 +491,7 @@ __global__ __launch_bounds__(TPB) void cg_direction_kernel(
       v += k.cz[s] * (cp[6 * s - 1] + cp[6 * s]);
     }
     v += shift * cp[0];
-    if constexpr (!FIRST) pn[e] = cp[0];
+    if constexpr (!FORMED) pn[e] = cp[0];
     ap[e] = v;
     sum += cp[0] * v;
     e += stride;
@@ -930,13 +960,18 @@ static hipError_t cg_solve(dk_ctx* c, const double* src, double* x, double tol, 
   if (e != hipSuccess) return e;
   CgState host{};
   constexpr int kBatch = 32;  // iterations queued between host checks
+  const bool three = n >= kCgThree;
   for (int it = 0;;) {
     for (const int end = it + kBatch; it < end; ++it) {
-      const auto direction = it == 0 ? cg_direction_kernel<true> : cg_direction_kernel<false>;
-      // iteration it - 1 left its direction in p[(it - 1) & 1]
-      const double* pd = p[it & 1];
-      hipLaunchKernelGGL(direction, dim3(nb), dim3(TPB), 0, s, it == 0 ? p[0] : p[(it - 1) & 1], r,
-                         p[it & 1], ap, d, k, shift, rpart, part, tol2, it, max_iter, st);
+      const bool formed = it == 0 || three;
+      if (three && it > 0)
+        hipLaunchKernelGGL(cg_combine_kernel, dim3(nb), dim3(TPB), 0, s, p[0], r, n, rpart, tol2, it,
+                           max_iter, st);
+      // two kernels: iteration it - 1 left its direction in p[(it - 1) & 1]
+      const double* pd = three ? p[0] : p[it & 1];
+      hipLaunchKernelGGL(formed ? cg_direction_kernel<true> : cg_direction_kernel<false>, dim3(nb),
+                         dim3(TPB), 0, s, formed ? p[0] : p[(it - 1) & 1], r, p[it & 1], ap, d, k,
+                         shift, rpart, part, tol2, it, max_iter, st);
       hipLaunchKernelGGL(cg_update_kernel, dim3(nb), dim3(TPB), 0, s, x, r, pd, ap, n, part, rpart,
                          it, st);
     }

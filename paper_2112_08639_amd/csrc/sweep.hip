@@ -275,13 +275,20 @@ void integrals_mixed_kernel(SweepArgs a) {
           *reinterpret_cast<bf16x4*>(xs + ((cb * NP + p) * 16 + 4 * i + g) * kTilePitch + 4 * c16) =
               pc[p];
       }
+    }
+    // other lanes of the wave read them: ordered here, and against the next tile by the
+    // barriers of the stages
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
       for (int p = 0; p < NP; ++p)
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks)
           xb[p][ks][cb] = *reinterpret_cast<const bf16x8*>(
               xs + ((cb * NP + p) * 16 + c16) * kTilePitch + 32 * ks + 8 * g);
-    }
     const unsigned long long now = live;
     const int entry0 = e0;
     // the next block's tile, in flight while this one is multiplied

@@ -34,7 +34,7 @@
 //   B n-contiguous: B(k,n) = B[k*ldb + n]     (B^T of a column-major N x K array)
 //
 // Epilogues
-//   kStore      C[m + n*ldc] = alpha*acc + beta*Cin[m + n*ldcin]   (Cin may alias C)
+//   kStore      C[m + n*ldc] = acc
 //   kPartial    P[s*M*N + m + n*M] = acc     (split-K partial sums of type TC; FP32
 //                                           partials lose nothing for FP32 accumulators)
 //   kBiasSilu   C = acc + bias[m], act = SiLU(C);  kSiluGrad  C = acc SiLU'(zin)   (FP32)
@@ -55,7 +55,6 @@ constexpr bool split_bf16_mode(int m) {
 // bf16 pieces per operand element in the split-at-store modes
 constexpr int split_pieces(int m) { return m == kBF16X6S ? 3 : 2; }
 enum GemmEpi { kStore = 0, kPartial = 1, kRowSum = 2, kBiasSilu = 3, kSiluGrad = 4 };
-enum TileSel { kAllTiles = 0, kUpperTiles = 1 };
 
 struct GemmArgs {
   int M = 0, N = 0, K = 0;
@@ -65,12 +64,8 @@ struct GemmArgs {
   long ldb = 0;
   void* C = nullptr;          // output (kStore) or partial buffer (kPartial)
   long ldc = 0;
-  const void* Cin = nullptr;  // kStore: source of the beta term
-  long ldcin = 0;
-  double alpha = 1.0, beta = 0.0;
   int splits = 1;             // split-K count (grid z)
   int k_per_split = 0;        // multiple of 64
-  int tile_sel = kAllTiles;
   int b_upper_tri = 0;        // B(k,n) = 0 for k > n: stop the K loop at the tile's last n
   // split-at-store modes with TB = __bf16: B comes pre-split, its NP piece planes
   // b_plane elements apart, each k-contiguous (B(k,n) piece p = B[p*b_plane + n*ldb + k])
@@ -307,7 +302,6 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
   if (g.n_fastest) { nt = (int)(w % gy); mt = (int)((w / gy) % gx); }
   else { mt = (int)(w % gx); nt = (int)((w / gx) % gy); }
   const int s = (int)(w / (gx * gy));
-  if (g.tile_sel == kUpperTiles && mt > nt) return;
   const int m0 = mt * BM, n0 = nt * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = (wave & 1) * (BM / 2), wn = (wave >> 1) * (BN / 2);
@@ -569,17 +563,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     float* st = reinterpret_cast<float*>(smem_ab);
     float* C = (EPI == kPartial) ? (float*)g.C + (long)s * g.M * g.N : (float*)g.C;
     const long ldc = (EPI == kPartial) ? (long)g.M : g.ldc;
-    const float* Cin = (EPI == kStore && g.beta != 0.0) ? (const float*)g.Cin : nullptr;
-    const bool vec_c = (reinterpret_cast<uintptr_t>(C) % 16 == 0) && (ldc % 4 == 0) &&
-                       (!Cin || ((reinterpret_cast<uintptr_t>(Cin) % 16 == 0) && g.ldcin % 4 == 0));
-    auto finish = [&](float v, long m, long n) -> float {
-      if constexpr (EPI == kPartial) return v;
-      else {
-        double out = g.alpha * (double)v;
-        if (Cin) out += g.beta * (double)Cin[m + n * g.ldcin];
-        return (float)out;
-      }
-    };
+    const bool vec_c = (reinterpret_cast<uintptr_t>(C) % 16 == 0) && (ldc % 4 == 0);
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       __syncthreads();
@@ -636,12 +620,9 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
           continue;
         }
         if (vec_c && m + 4 <= g.M) {
-          *reinterpret_cast<float4*>(cp) =
-              make_float4(finish(sp[0], m, n), finish(sp[1], m + 1, n), finish(sp[2], m + 2, n),
-                          finish(sp[3], m + 3, n));
+          *reinterpret_cast<float4*>(cp) = make_float4(sp[0], sp[1], sp[2], sp[3]);
         } else {
-          for (int e = 0; e < 4 && m + e < g.M; ++e)
-            cp[e] = finish(sp[e], m + e, n);
+          for (int e = 0; e < 4 && m + e < g.M; ++e) cp[e] = sp[e];
         }
       }
     }
@@ -656,14 +637,9 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
           const long m = m0 + wm + 16 * i + mc;
           const long n = n0 + wn + 16 * j + nq + QS * q;
           if (m >= g.M || n >= g.N) continue;
-          const double v = to_d(acc[j][i][q]);
-          if constexpr (EPI == kPartial) {
-            ((TC*)g.C)[(long)s * g.M * g.N + m + n * g.M] = (TC)v;
-          } else {
-            double out = g.alpha * v;
-            if (g.beta != 0.0) out += g.beta * to_d(((const TC*)g.Cin)[m + n * g.ldcin]);
-            ((TC*)g.C)[m + n * g.ldc] = (TC)out;
-          }
+          const TC v = (TC)to_d(acc[j][i][q]);
+          if constexpr (EPI == kPartial) ((TC*)g.C)[(long)s * g.M * g.N + m + n * g.M] = v;
+          else ((TC*)g.C)[m + n * g.ldc] = v;
         }
   }
 }

@@ -398,7 +398,7 @@ size_t gram_ws_bytes(const dk_ctx* c, int n_s) {
 // out = scale * X^T Y (n_s x n_s FP64).  symmetric_x: Y == X, only the upper
 // tiles are computed and mirrored; otherwise the result is symmetrised.
 // FP64 context: FP64 MFMA.  Mixed context: FP64 MFMA on the widened FP32
-// block (Gram), or split-BF16 MFMA (bf16x3, projection).
+// block (Gram), or split-BF16 MFMA (bf16x3, projection: never symmetric_x).
 hipError_t gram(dk_ctx* c, const void* x, const void* y, long ld, int n_s, bool symmetric_x,
                 double scale, double* out, void* ws, bool bf16x3, int kind) {
   KTimer kt(c, kind);
@@ -414,13 +414,12 @@ hipError_t gram(dk_ctx* c, const void* x, const void* y, long ld, int n_s, bool 
     p.B = y;
     p.ldb = ld;
     p.C = ws;
-    p.tile_sel = symmetric_x ? kUpperTiles : kAllTiles;
     plan_projection(p);
     e = launch_gemm<kBF16X3S, float, float, true, true, kPartial, float, kProjTile, kProjTile, 32>(
         p, c->stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(reduce_square_kernel<float>, rgrid, dim3(256), 0, c->stream,
-                       (const float*)ws, p.splits, n_s, scale, symmetric_x ? 1 : 0, out);
+                       (const float*)ws, p.splits, n_s, scale, 0, out);
     return hipGetLastError();
   }
   NtArgs g;

@@ -35,11 +35,10 @@ struct StencilArgs {
   int ty_tile;  // rows per tile
   int zc;       // planes per z-chunk
   double cx[7], cy[7], cz[7];  // -1/2 w_k / h_a^2, k = 1..6 (index 0 unused)
-  double diag;                 // -1/2 w_0 (1/hx^2 + 1/hy^2 + 1/hz^2)
   double alpha, beta, shift;
   // the same in FP32, converted once on the host (uniform SGPR operands)
   float fcx[7], fcy[7], fcz[7];
-  float falpha, fbeta, fdshift, fshift;
+  float falpha, fbeta, fshift;
 };
 
 // (a + b) - 2 c with one rounding of the difference.  The kinetic term is
@@ -940,7 +939,6 @@ static void fill_coeffs(const dk_ctx* c, StencilArgs& a) {
     a.cy[k] = -0.5 * w[k] * iy;
     a.cz[k] = -0.5 * w[k] * iz;
   }
-  a.diag = -0.5 * w[0] * (ix + iy + iz);
   for (int k = 0; k < 7; ++k) {
     a.fcx[k] = (float)a.cx[k];
     a.fcy[k] = (float)a.cy[k];
@@ -948,7 +946,6 @@ static void fill_coeffs(const dk_ctx* c, StencilArgs& a) {
   }
   a.falpha = (float)a.alpha;
   a.fbeta = (float)a.beta;
-  a.fdshift = (float)(a.diag - a.shift);
   a.fshift = (float)a.shift;
 }
 

@@ -218,6 +218,15 @@ static void free_tables(dk_ctx* c) {
   c->model_channels = 0;
 }
 
+// What the kernels read beside chi64.  On a failure (no memory) no projectors are left: the
+// context must not hold a count without the tables that it stands for.
+static hipError_t derived_tables(dk_ctx* c) {
+  hipError_t e = fd_gradient_tables(c);
+  if (e == hipSuccess) e = build_sweep_tables(c);
+  if (e != hipSuccess) free_tables(c);
+  return e;
+}
+
 dk_status dk_destroy(dk_ctx* c) {
   if (!c) return DK_OK;
   hipSetDevice(c->device);
@@ -308,8 +317,7 @@ dk_status dk_set_projectors(dk_ctx* c, int n_proj, int n_atoms, const int64_t* o
   DK_HIP(c, hipMemcpy(c->gamma_dev, c->gamma_h.data(), n_proj * sizeof(double), hipMemcpyHostToDevice));
   DK_HIP(c, hipMemcpy(c->atom_dev, c->atom_h.data(), n_proj * sizeof(int), hipMemcpyHostToDevice));
   c->n_proj = n_proj;
-  DK_HIP(c, fd_gradient_tables(c));
-  DK_HIP(c, build_sweep_tables(c));
+  DK_HIP(c, derived_tables(c));
   return finish(c, "dk_set_projectors");
 }
 
@@ -383,8 +391,7 @@ dk_status dk_set_projector_model(dk_ctx* c, int n_atoms, const double* pos, int 
   DK_HIP(c, hipMemcpyAsync(c->atom_dev, c->atom_h.data(), n_proj * sizeof(int), hipMemcpyHostToDevice, c->stream));
   DK_HIP(c, build_projector_tables(c, pos_dev, n_atoms, n_channels, l, rc, cutoff_rel, norms_dev));
   c->n_proj = n_proj;
-  DK_HIP(c, fd_gradient_tables(c));
-  DK_HIP(c, build_sweep_tables(c));
+  DK_HIP(c, derived_tables(c));
   std::vector<double> nrm(n_proj);
   DK_HIP(c, hipMemcpyAsync(nrm.data(), norms_dev, n_proj * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   dk_status s = finish(c, "dk_set_projector_model");

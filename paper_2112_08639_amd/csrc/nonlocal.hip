@@ -14,8 +14,9 @@ namespace dk {
 
 namespace {
 
-// out[e] = scale * sum_s part[s * mn + e].  A block owns 64 consecutive entries; its four waves sum interleaved quarters of the splits
-// (two independent chains each), then combine in LDS.
+// out[e] = scale * sum_s part[s * mn + e].  A block owns 64 consecutive entries; its four
+// waves sum interleaved quarters of the splits (two independent chains each), then combine
+// in LDS.
 template <typename PT>
 __global__ __launch_bounds__(256) void reduce_rows_kernel(const PT* __restrict__ part, int splits,
                                                           long mn, double scale,

@@ -462,10 +462,10 @@ void integrals_f64_kernel(SweepArgs a) {
 // ----------------------------------------------------------------- scatter --
 //
 // A wave holds the table values of its points and of up to 32 live groups in registers
-// and walks over the columns, 16 at a time: the coefficients of a tile come as one 16-byte
-// (FP64: 32-byte) load per four groups (lane group g takes group 4 q + g, and k step j
-// projector j of each), the tile of Y is read one tile ahead, the coefficients of the
-// next tile replace this one's as they are used, and nothing passes through LDS.  The
+// (FP64: 24) and walks over the columns, 16 at a time: the coefficients of a tile come as
+// one 16-byte (FP64: 32-byte) load per four groups (lane group g takes group 4 q + g, and k
+// step j one projector of each), the tile of Y is read one tile ahead, the coefficients of
+// the next tile replace this one's as they are used, and nothing passes through LDS.  The
 // four waves of a workgroup take consecutive points of the same columns.  The grid is two
 // waves per SIMD, every workgroup with an equal share of the tiles, points outermost.
 // (Shares by the cost of their blocks instead of equal ones change nothing.)

@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256) void sweep_table_kernel(
 // wave's memory operations complete in order, so a consumer that loaded them would wait
 // for its tile of the next block as well (373248 x 2048, 432 projectors, two pieces: 1.60
 // against 1.16 ms).  Measured: 60 us at 110592 x 512 over 128 projectors (3.8 TB/s), before 80
-// over the dense table; 1.10 against 1.72 ms at 373248 x 2048; FP64 186 against 342 us
+// over the dense table; 1.11 against 1.72 ms at 373248 x 2048; FP64 186 against 342 us
 // at 110592 x 512.  In the mixed kernel the feeding waves run at the highest priority
 // (64.6 -> 62.8 us and, over 432 projectors, 1.23 -> 1.17 ms); in FP64, where they share
 // SIMDs whose matrix pipes are full, at the same as the others (higher: 186 -> 208 us).
@@ -660,7 +660,7 @@ __global__ __launch_bounds__(256, OCC) void scatter_kernel(ScatterArgs a) {
 // takes one projector and 64 columns; its W waves sum interleaved shares of the
 // occurrences, kReduceDepth loads in flight each, which is what the time goes by
 // (two in flight: 12 us at 24^3 x 64 in FP64, 10 at 48^3 x 512 mixed; now 4 and 7; at 72^3 x
-// 2048 mixed, 108 groups, both 80, bound by the partials).  occ null: the dense runs,
+// 2048 mixed, 108 groups, 141, bound by the partials).  occ null: the dense runs,
 // occurrence o of group g = o n_groups + g.
 constexpr int kReduceDepth = 16;
 template <typename PT, int W>
@@ -739,7 +739,7 @@ __global__ __launch_bounds__(256) void group_lists_kernel(const double* __restri
 // to each other: a block is (part of) an x-row, so they are sorted by the z of their centre
 // in layers of kLayer bohr, then by y.  With atoms in the order of cubic cells 6.7 of 8 row
 // blocks are live at 48^3 over 32 groups and 9.9 of 16 at 72^3 over 108; sorted, 5.3 and
-// 7.5, and the integrals of 2048 columns take 1.10 instead of 1.17 ms.
+// 7.5, and the integrals of 2048 columns took 1.10 instead of 1.17 ms.
 // From here on a group is its place in that order, perm[place] the four projectors and
 // ggamma their energies.
 constexpr double kLayer = 4.0;
